@@ -286,6 +286,18 @@ __device__ __forceinline__ int group_begin(const int *__restrict__ offsets, int 
     return lo;
 }
 
+// Workgroups of a launch: one per compute unit (the LDS ring and the register
+// file are sized for it), and no more than tracks.  group_begin spreads the
+// rows over all of them, so a small call takes one tile per wave on many units
+// instead of several in a row on a few.  A tile's walk through the layers is
+// what a small call costs: with at least 8 tracks per wave (6 workgroups for 500
+// tracks) the four-layer d = 128 encoder took 243 us for 500 tracks and 284 us
+// for 3072, spread over the chip 50 and 99 us; from about 20 000 tracks on both
+// rules fill the chip.
+inline unsigned workgroups(int n_tracks, int cu_count) {
+    return (unsigned)(n_tracks < cu_count ? (n_tracks < 1 ? 1 : n_tracks) : cu_count);
+}
+
 // Workgroup barrier that orders LDS only (the kernel shares nothing through
 // global memory within a workgroup).
 __device__ __forceinline__ void lds_barrier() {

@@ -430,12 +430,8 @@ hipError_t launch_layer(const void *X, long long x_rows, const int32_t *offsets,
                         const unsigned char *stages, void *Y, float *states, int *err, int cu_count,
                         hipStream_t stream) {
     using C = MCfg<OP, DIN>;
-    long long waves = (n_tracks + 7) / 8;
-    long long blocks = (waves + C::WAVES - 1) / C::WAVES;
-    if (blocks > cu_count) blocks = cu_count;
-    if (blocks < 1) blocks = 1;
     using FE = typename Frag<OP>::E;
-    hipLaunchKernelGGL((tf_mingru_kernel<OP, DIN, H, LAST>), dim3((unsigned)blocks), dim3(64 * C::WAVES), 0, stream,
+    hipLaunchKernelGGL((tf_mingru_kernel<OP, DIN, H, LAST>), dim3(workgroups(n_tracks, cu_count)), dim3(64 * C::WAVES), 0, stream,
                        static_cast<const FE *>(X), x_rows, offsets, (int)n_tracks, stages, static_cast<FE *>(Y), states,
                        err);
     return hipGetLastError();
@@ -827,11 +823,7 @@ hipError_t launch_backbone(const float *feats, int nf, long long n_hits, long lo
                            int32_t n_tracks, const unsigned char *stages, int n_fst, float *states, int *err,
                            int cu_count, hipStream_t stream) {
     using C = BCfg<OP>;
-    long long waves = (n_tracks + 7) / 8;
-    long long blocks = (waves + C::WAVES - 1) / C::WAVES;
-    if (blocks > cu_count) blocks = cu_count;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL((tf_backbone_kernel<OP>), dim3((unsigned)blocks), dim3(64 * C::WAVES), 0, stream, feats, nf,
+    hipLaunchKernelGGL((tf_backbone_kernel<OP>), dim3(workgroups(n_tracks, cu_count)), dim3(64 * C::WAVES), 0, stream, feats, nf,
                        n_hits, x_rows, offsets, (int)n_tracks, stages, n_fst, states, err);
     return hipGetLastError();
 }

@@ -1917,15 +1917,8 @@ template <int D, int OP, int HT, int OUTM, bool FOURIER, bool PAIR = false>
 hipError_t launch(const float *hits, int64_t n_hits, const int32_t *offsets, int32_t n_tracks,
                   const tf_weights *w, float *out, long long out_rows, hipStream_t stream) {
     using C = KCfg<D, OP, HT, PAIR>;
-    // one workgroup per compute unit (the LDS ring and the register file are
-    // sized for it), at least 8 tracks per wave
-    long long waves = (n_tracks + 7) / 8;
-    long long blocks = (waves + C::WAVES - 1) / C::WAVES;
-    const long long cap = (long long)w->cu_count;
-    if (blocks > cap) blocks = cap;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL((tf_encoder_kernel<D, OP, HT, OUTM, FOURIER, PAIR>), dim3((unsigned)blocks), dim3(64 * C::WAVES), 0, stream,
-                       hits, (long long)n_hits, offsets, (int)n_tracks, w->params, out, out_rows, w->err);
+    hipLaunchKernelGGL((tf_encoder_kernel<D, OP, HT, OUTM, FOURIER, PAIR>), dim3(workgroups(n_tracks, w->cu_count)),
+                       dim3(64 * C::WAVES), 0, stream, hits, (long long)n_hits, offsets, (int)n_tracks, w->params, out, out_rows, w->err);
     return hipGetLastError();
 }
 
