@@ -167,97 +167,149 @@ __device__ __forceinline__ void copy_stage(const unsigned char *stages, int s, u
     }
 }
 
-// Packing of one wave tile from a window of up to 32 tracks, one per lane
-// (lanes 0..31; len: that lane's track length).  cand: the window lanes that
-// may join the tile, each at most CAP long.  The tile takes the oldest
-// candidate, then (PAIR) the one or two other candidates whose lengths fill
-// the remaining rows best (the lowest lanes among equals), then the rest
-// first-fit in window order, up to MAXTR tracks and CAP rows.  A track's result does not
-// depend on the tile it lands in, so the packing only decides how full the
-// tiles are (about 94 % for lengths 8..20 in 32 rows, against 90 % for plain
-// first-fit).  Returns the selected lanes (wave-uniform); rows: their total
-// length.  The length masks are built in scalar registers, one candidate at a
-// time, so the packing issues no cross-lane traffic through LDS.  Without PAIR
-// the tile is plain first-fit from the oldest candidate: cheaper per tile,
-// for kernels whose tiles are short enough that the search does not pay.
-template <int CAP, int MAXTR, bool PAIR>
-__device__ __forceinline__ unsigned pack_tile(unsigned cand, int len, int lane, int &rows) {
-    static_assert(CAP <= 64 && MAXTR >= 3, "tile shape");
-    typedef unsigned long long u64;
-    const int first = __builtin_ctz(cand);
-    int n = __builtin_amdgcn_readlane(len, first);
-    unsigned sel = 1u << first;
-    const unsigned rest = cand & ~sel;
-    const int room = CAP - n;
-    if constexpr (PAIR) {
-        // bit l - 1 of m1: a length l among the other candidates that fit beside
-        // the first; of m2: one that at least two of them have
-        u64 m1 = 0, m2 = 0;
-        for (unsigned c = rest; c; c &= c - 1u) {
-            const int li = __builtin_amdgcn_readlane(len, __builtin_ctz(c));
-            if (li <= room) {
-                const u64 b = 1ull << (li - 1);
-                m2 |= m1 & b;
-                m1 |= b;
-            }
-        }
-        auto upto = [](int r) -> u64 { return r <= 0 ? 0ull : r >= 64 ? ~0ull : (1ull << r) - 1ull; };
-        const u64 ms = m1 & upto(room);
-        const int single = ms ? 64 - __builtin_clzll(ms) : 0;
-        // per candidate lane: the longest other length that fits beside it
-        const bool av = lane < 32 && ((rest >> (lane & 31)) & 1u) && len <= room;
-        int pair = 0, partner = 0;
-        if (av) {
-            const int left = room - len;
-            u64 m = m1 & upto(left);
-            if (len <= left && !((m2 >> (len - 1)) & 1ull)) m &= ~(1ull << (len - 1));  // not itself
-            if (m) {
-                partner = 64 - __builtin_clzll(m);
-                pair = len + partner;
-            }
-        }
-        // the best pair sum above the best single, counted down from the room left
-        int best = 0;
-        unsigned long long who = 0;
-        for (int sum = room; sum > single; --sum) {
-            who = __ballot(av && pair == sum);
-            if (who) {
-                best = sum;
-                break;
-            }
-        }
-        if (best) {
-            const int i = __builtin_ctzll(who);
-            const int pl = __builtin_amdgcn_readlane(partner, i);
-            const bool mate = lane < 32 && lane != i && ((rest >> (lane & 31)) & 1u) && len == pl;
-            const int j = __builtin_ctzll(__ballot(mate));
-            sel |= (1u << i) | (1u << j);
-            n += best;
-        } else if (single > 0) {
-            sel |= 1u << __builtin_ctzll(__ballot(av && len == single));
-            n += single;
-        }
+// The tracks that a few waves of a workgroup still have to fit between them: the
+// first not yet in a tile (t), the end of their range, and for the 64 tracks
+// from t on the ones already in a tile or refused (bit i of taken: track t + i).
+// Each of those waves keeps the same copy in scalar registers.
+struct TrackPool {
+    int t, end;
+    unsigned long long taken;
+    // past the leading tracks that are done
+    __device__ __forceinline__ void slide() {
+        const int sh = taken == ~0ull ? 64 : __builtin_ctzll(~taken);
+        taken = sh == 64 ? 0ull : taken >> sh;
+        t += sh;
     }
-    // first-fit over the rest, in window order.  A lane passed over once never
-    // fits later (the rows only fill up), so each step takes the lowest remaining
-    // lane whose track fits the rows left: one ballot per track taken.
-    int k = __builtin_popcount(sel);
-    unsigned left = rest & ~sel;
-    while (left && k < MAXTR && n < CAP) {
-        const unsigned fit = left & unsigned(__ballot(lane < 32 && len <= CAP - n));
-        if (!fit) break;
-        const int i = __builtin_ctz(fit);
-        n += __builtin_amdgcn_readlane(len, i);
-        sel |= 1u << i;
-        left &= ~(1u << i);
-        ++k;
-    }
-    rows = n;
-    return sel;
+};
+
+// The offsets of the pool's next window, straight into LDS (win_lds: byte address
+// of 2 x 64 ints): track t + lane's, then the one after it.  One wave's job, after
+// the barrier that follows a round's packing; in place at the next barrier that
+// this wave passes with its loads complete.  (Read by every wave at the start of a
+// round they cost it the latency of a first touch.)
+constexpr int kWindowBytes = 2 * 64 * 4;
+__device__ __forceinline__ void lds_dma4(const void *gsrc, unsigned lds_addr) {
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %0, off"
+                 :
+                 : "v"(gsrc), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
+                 : "memory");
+}
+__device__ __forceinline__ void prefetch_window(const int *__restrict__ offsets, TrackPool p, unsigned win_lds,
+                                                int lane) {
+    p.slide();
+    const int idx = p.t + lane;
+    lds_dma4(offsets + (idx < p.end ? idx : p.end), win_lds);
+    lds_dma4(offsets + (idx + 1 < p.end ? idx + 1 : p.end), win_lds + 256);
 }
 
-// First track of wave group g of ng: the tracks are split into ng contiguous
-// groups of about equal hit rows.  The result is the number of tracks i with
+// One tile per wave for TILES waves, from the pool they share.  Each of them runs
+// the same packing of all TILES tiles over the same offsets and keeps tile `me`, so
+// they agree on the pool's next state without any exchange.  A tile takes the
+// oldest track left, then, until it is full: a track that fills its CAP rows
+// exactly, else the first that leaves room for the shortest track of the window,
+// else the first that fits; up to MAXTR tracks.
+// A track's result does not depend on the tile it lands in, so the packing only
+// decides how full the tiles are and how many the slowest wave takes.  Each wave
+// packing a range of its own first-fit gave, with lengths 8..20 and 262 144
+// tracks on 256 workgroups of 12 waves, 41.4 tiles per wave on average but 46 for
+// the slowest wave of the launch; the exact fits and pools of 4 waves give 38.6
+// and 41.  (Pools of all 12 give 38.3 and 39, but a step of the packing, about 25
+// dependent instructions, takes a wave some 300 cycles, and each wave runs the
+// steps of its whole pool: they made a round of 12 tiles 2.3 us longer.)
+// win: the offsets of the first window (prefetch_window); later ones of the same
+// round are read from memory.
+// Tracks that cannot be fitted (rows outside [lo, hi), an end before the
+// start, no hits, more than CAP) are handed to refuse(bad, empty, too_long: lane
+// masks, track index of this lane).  Tile me's track table goes to tab (first
+// tile row, length, first hit row, track index: MAXTR ints each), its track count
+// to k, its rows to n and the mask of its rows that start a track to smask.
+// Returns the number of tiles formed, the same in every wave (0: the pool is empty).
+template <int CAP, int MAXTR, int TILES, class Refuse>
+__device__ __forceinline__ int pool_pack(const int *__restrict__ offsets, const int *win, TrackPool &p, long long lo,
+                                         long long hi, int me, int lane, int *tab, int &k, int &n,
+                                         unsigned long long &smask, Refuse refuse) {
+    static_assert(CAP <= 64 && MAXTR <= 255, "tile shape");
+    typedef unsigned long long u64;
+    int my_pos = 0, tiles = 0;  // my_pos: rows + 256 tracks of tile me
+    u64 my_rows = 0;
+    bool first = true;
+    for (;;) {
+        // the oldest track left goes into the next tile, so every turn moves on
+        p.slide();
+        if (tiles >= TILES || p.t >= p.end) break;
+        const int idx = p.t + lane;
+        const bool in = idx < p.end;
+        int off = 0, nxt = 0;
+        if (first) {
+            off = win[lane];
+            nxt = win[64 + lane];
+        } else if (in) {
+            off = offsets[idx];
+            nxt = offsets[idx + 1];
+        }
+        first = false;
+        const u64 fresh = __ballot(in) & ~p.taken;
+        const bool bad = nxt < off || (long long)off < lo || (long long)nxt > hi;
+        const int len = bad ? -1 : nxt - off;
+        u64 av = fresh & __ballot(len > 0 && len <= CAP);
+        const u64 refused = fresh & ~av;
+        if (refused) {
+            const u64 bad_m = refused & __ballot(bad), empty_m = refused & __ballot(len == 0);
+            refuse(bad_m, empty_m, refused & ~bad_m & ~empty_m, idx);
+            p.taken |= refused;
+        }
+        if (!av) continue;
+        // shortest track of the window: the lowest length bit by bit
+        int mn = 0;
+#pragma unroll
+        for (int b = CAP; b; b >>= 1) mn += (av & __ballot(len < mn + b)) ? 0 : b;
+        const bool more = p.end - p.t > 64;
+        int place = 0;   // this lane's tile row + 256 x its place in the tile
+        u64 my_sel = 0;  // lanes of tile me
+        do {
+            int room = CAP, pos = 0;
+            u64 rows = 0, m = av;
+            const u64 before = av;
+            do {
+                const int i = __builtin_ctzll(m);
+                const int li = __builtin_amdgcn_readlane(len, i);
+                asm("s_bitset0_b64 %0, %1" : "+s"(av) : "s"(i));
+                asm("s_bitset1_b64 %0, %1" : "+s"(rows) : "s"(pos));  // (bit pos % 64: the tile row)
+                place = lane == i ? pos : place;
+                room -= li;
+                pos += li + 256;
+                const u64 m1 = av & __ballot(len == room), m2 = av & __ballot(len <= room - mn),
+                          m3 = av & __ballot(len <= room);
+                m = m1 ? m1 : m2 ? m2 : m3;
+            } while (m && pos < 256 * MAXTR);
+            const u64 sel = before & ~av;
+            p.taken |= sel;
+            if (tiles == me) {
+                my_sel = sel;
+                my_rows = rows;
+                my_pos = pos;
+            }
+            ++tiles;
+            // (few candidates left make poor tiles: read on, if there are more)
+        } while (tiles < TILES && av && !(more && __builtin_popcountll(av) < 24));
+        if ((my_sel >> lane) & 1ull) {
+            int *e = tab + (place >> 8);
+            e[0] = place & 255;
+            e[MAXTR] = len;
+            e[2 * MAXTR] = off;
+            e[3 * MAXTR] = idx;
+        }
+    }
+    // (uniform already, but not for the compiler)
+    k = uniform(my_pos >> 8);
+    n = uniform(my_pos & 255);
+    smask = (u64)(unsigned)uniform(int(unsigned(my_rows))) |
+            ((u64)(unsigned)uniform(int(unsigned(my_rows >> 32))) << 32);
+    return uniform(tiles);
+}
+
+// First track of group g of ng: the tracks are split into ng contiguous groups
+// (one per workgroup) of about equal hit rows.  The result is the number of tracks i with
 // offsets[i] < offsets[0] + R g / ng (R: the rows of all tracks), found by a
 // 64-ary search that follows the leading run of true probes; that count grows
 // with the target for any offsets array, so the groups of consecutive g tile
@@ -288,12 +340,11 @@ __device__ __forceinline__ int group_begin(const int *__restrict__ offsets, int 
 
 // Workgroups of a launch: one per compute unit (the LDS ring and the register
 // file are sized for it), and no more than tracks.  group_begin spreads the
-// rows over all of them, so a small call takes one tile per wave on many units
-// instead of several in a row on a few.  A tile's walk through the layers is
-// what a small call costs: with at least 8 tracks per wave (6 workgroups for 500
-// tracks) the four-layer d = 128 encoder took 243 us for 500 tracks and 284 us
-// for 3072, spread over the chip 50 and 99 us; from about 20 000 tracks on both
-// rules fill the chip.
+// rows over all of them, so a small call takes few tiles on many units instead of
+// several in a row on a few.  A tile's walk through the layers is what a small
+// call costs: with at least 8 tracks per wave (6 workgroups for 500 tracks) the
+// four-layer d = 128 encoder took 243 us for 500 tracks, spread over the chip
+// 39 us; from about 20 000 tracks on both rules fill the chip.
 inline unsigned workgroups(int n_tracks, int cu_count) {
     return (unsigned)(n_tracks < cu_count ? (n_tracks < 1 ? 1 : n_tracks) : cu_count);
 }

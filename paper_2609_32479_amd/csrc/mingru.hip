@@ -46,6 +46,7 @@ namespace {
 constexpr int kMgCap = 32;    // hits per wave tile
 constexpr int kMgMaxTr = 16;  // tracks per wave tile
 constexpr int kMgSP = 16;     // positions per stream (two streams per tile)
+constexpr int kMgTPP = 4;     // waves that share a pool of tracks (pool_pack)
 
 template <int OP, int DIN>
 struct MCfg {
@@ -58,11 +59,12 @@ struct MCfg {
     // 16-bit operands: two waves per SIMD (256 registers: the input operands
     // take DIN / 4); fp32 operands: one (DIN / 2 of the 512)
     static constexpr int WAVES = HALF ? 8 : 4;
+    static constexpr int NPOOL = WAVES / kMgTPP;
     // one weight block: a 32-row slice of the candidate or gate rows, then its 32 biases
     static constexpr int BLOCK = round_up(KIN * FRAG + 32 * 4, 16);
     // a stage holds one block, or both blocks of a chunk and direction when two
     // slots of that size still leave room for a ring of at least three
-    static constexpr bool MERGE = 3 * round_up(2 * BLOCK, kCopyBytes) + WAVES * (4 * kMgMaxTr * 4 + kMgCap * 4 + kMgCap * (32 * EB + 16)) <= kLdsBytesMax;
+    static constexpr bool MERGE = 3 * round_up(2 * BLOCK, kCopyBytes) + WAVES * (4 * kMgMaxTr * 4 + kMgCap * 4 + kMgCap * (32 * EB + 16)) + NPOOL * kWindowBytes + 16 <= kLdsBytesMax;
     static constexpr int STAGE = round_up((MERGE ? 2 : 1) * BLOCK, kCopyBytes);
     static constexpr int SPC = MERGE ? 1 : 2;  // stages per chunk and direction
     static constexpr int COPIES = STAGE / kCopyBytes;
@@ -72,11 +74,13 @@ struct MCfg {
     static constexpr int ROWB = 32 * EB + 16;
     static constexpr int TB_OFF = 4 * kMgMaxTr * 4 + kMgCap * 4;
     static constexpr int WAVE_BYTES = TB_OFF + kMgCap * ROWB;
-    static constexpr int NSLOT_FIT = (kLdsBytesMax - WAVES * WAVE_BYTES) / STAGE;
+    static constexpr int NSLOT_FIT = (kLdsBytesMax - WAVES * WAVE_BYTES - NPOOL * kWindowBytes - 16) / STAGE;
     static constexpr int NSLOT = NSLOT_FIT > 4 ? 4 : NSLOT_FIT;
     static_assert(NSLOT >= 2, "stage ring");
     static constexpr int WAVE0 = NSLOT * STAGE;
-    static constexpr int LDS_BYTES = WAVE0 + WAVES * WAVE_BYTES;
+    static constexpr int WIN_OFF = WAVE0 + WAVES * WAVE_BYTES;  // the pools' next windows (pool_pack)
+    static constexpr int FLAG_OFF = WIN_OFF + NPOOL * kWindowBytes;  // the tile flag
+    static constexpr int LDS_BYTES = FLAG_OFF + 16;
     static_assert(DIN % K == 0, "input width");
 };
 
@@ -110,85 +114,81 @@ __device__ __forceinline__ void scan_dir(float (&ax)[kMgSP], float (&cf)[kMgSP],
     }
 }
 
-// Tiles are packed from a window of a wave's tracks: the first track not yet
-// fitted (t) and the kMgWin - 1 after it; bit i of `taken` marks track t + i as
-// fitted into an earlier tile (or refused).  A track that cannot be fitted
-// (rows below 0 or row0, past row0 + x_rows or n_hits, no hits, more than 32)
-// is refused: its error bit and, with states, NaN end states (2H of them).
-// Returns the tile's window lanes (sel; wave-uniform) and their row total (n);
-// off and len are each window lane's track start and length.
-constexpr int kMgWin = 32;
-__device__ __forceinline__ unsigned mg_select(const int *__restrict__ offsets, int g_end, int row0, long long x_rows,
-                                              long long n_hits, int lane, int &t, unsigned &taken, int &errbits,
-                                              float *__restrict__ states, int H, int &n, int &off, int &len) {
-    n = 0;
-    off = 0;
-    len = 0;
-    while (t < g_end) {
-        const int sh = taken == ~0u ? kMgWin : __builtin_ctz(~taken);
-        taken = sh == kMgWin ? 0u : taken >> sh;
-        t += sh;
-        if (t >= g_end) break;
-        const int idx = t + lane;
-        off = (lane <= kMgWin && idx <= g_end) ? offsets[idx] : 0;
-        const int nxt = __shfl_down(off, 1);
-        len = nxt - off;
-        const bool fresh = lane < kMgWin && idx < g_end && !((taken >> (lane & 31)) & 1u);
-        const bool bad_rows =
-            off < 0 || off < row0 || nxt < off || (long long)nxt - row0 > x_rows || (long long)nxt > n_hits;
-        const bool empty = !bad_rows && len == 0;
-        const bool too_long = !bad_rows && len > kMgCap;
-        const unsigned bm = unsigned(__ballot(fresh && bad_rows));
-        const unsigned em = unsigned(__ballot(fresh && empty));
-        const unsigned lm = unsigned(__ballot(fresh && too_long));
-        if (bm | em | lm) {
-            errbits |= (bm ? TF_DEVERR_BAD_OFFSETS : 0) | (em ? TF_DEVERR_EMPTY_TRACK : 0) |
-                       (lm ? TF_DEVERR_TOO_LONG : 0);
-            if (states) {
-                const float qnan = __builtin_nanf("");
-                for (unsigned m = bm | em | lm; m; m &= m - 1u)
-                    for (int e = lane; e < 2 * H; e += 64) states[(size_t)(t + __builtin_ctz(m)) * 2 * H + e] = qnan;
-            }
-            taken |= bm | em | lm;
+// A wave's share of a workgroup's work: its pool (a contiguous range of tracks
+// balanced by hit rows, shared by kMgTPP waves), its place among the pool's
+// waves, the pool's window and the workgroup's tile flag.
+struct MgWork {
+    TrackPool pool;
+    int me, round;
+    const int *win;
+    unsigned win_lds;
+    int *flag;
+    template <class C>
+    __device__ __forceinline__ void begin(char *smem, unsigned smem_lds, const int *__restrict__ offsets, int n_tracks,
+                                          int wid, int lane) {
+        const int pid = uniform(wid / kMgTPP);
+        me = uniform((wid + pid) % kMgTPP);  // (the pools' first tiles on different SIMDs)
+        const long long g = (long long)blockIdx.x * C::NPOOL + pid, ng = (long long)gridDim.x * C::NPOOL;
+        pool.t = uniform(group_begin(offsets, n_tracks, g, ng, lane));
+        pool.end = uniform(group_begin(offsets, n_tracks, g + 1, ng, lane));
+        pool.taken = 0;
+        win = reinterpret_cast<const int *>(smem + C::WIN_OFF + pid * kWindowBytes);
+        win_lds = smem_lds + C::WIN_OFF + pid * kWindowBytes;
+        flag = reinterpret_cast<int *>(smem + C::FLAG_OFF);
+        round = 0;
+        if (me == 0) {
+            prefetch_window(offsets, pool, win_lds, lane);
+            wait_vmcnt<0>();
         }
-        const unsigned cand = unsigned(__ballot(fresh && !bad_rows && !empty && !too_long));
-        if (cand) {
-            const unsigned sel = pack_tile<kMgCap, kMgMaxTr, true>(cand, len, lane, n);
-            taken |= sel;
-            return sel;
-        }
+        if (threadIdx.x == 0) *flag = 0;
+        lds_barrier();
     }
-    return 0u;
-}
+    // The wave's next tile: k tracks, n rows, the mask of the rows that start a
+    // track and the track table t_start [4][kMgMaxTr]; false when no wave of the
+    // workgroup has one.  Waits for the wave's copies and passes a barrier.  A
+    // track that cannot be fitted (rows below 0 or row0, past row0 + x_rows or
+    // n_hits, no hits, more than 32) is refused: its error bit and, with states,
+    // NaN end states (2H of them).
+    __device__ __forceinline__ bool next(const int *__restrict__ offsets, int row0, long long x_rows, long long n_hits,
+                                         int &errbits, float *__restrict__ states, int H, int *t_start,
+                                         int &k, int &n, unsigned long long &smask) {
+        // (lane values read afresh: held across a tile's layers they would take
+        // registers that the layers' operands need)
+        const long long lo = row0 > 0 ? row0 : 0, top = (long long)row0 + x_rows;
+        pool_pack<kMgCap, kMgMaxTr, kMgTPP>(
+            offsets, win, pool, lo, top < n_hits ? top : n_hits, me, fresh_lane(), t_start, k, n, smask,
+            [&](unsigned long long bm, unsigned long long em, unsigned long long lm, int) {
+                if (me != 0) return;
+                errbits |= (bm ? TF_DEVERR_BAD_OFFSETS : 0) | (em ? TF_DEVERR_EMPTY_TRACK : 0) |
+                           (lm ? TF_DEVERR_TOO_LONG : 0);
+                if (states) {
+                    const float qnan = __builtin_nanf("");
+                    for (unsigned long long m = bm | em | lm; m; m &= m - 1ull)
+                        for (int e = fresh_lane(); e < 2 * H; e += 64)
+                            states[(size_t)(pool.t + __builtin_ctzll(m)) * 2 * H + e] = qnan;
+                }
+            });
+        wait_vmcnt<0>();
+        ++round;
+        // a wave with a tile writes the round's number; the workgroup stops at the
+        // first round that no wave wrote (the next write comes after later barriers)
+        if (k > 0 && fresh_lane() == 0) *flag = round;
+        lds_barrier();
+        if (uniform(*flag) != round) return false;
+        if (me == 0) prefetch_window(offsets, pool, win_lds, fresh_lane());
+        return true;
+    }
+};
 
-// Track table and masks of a packed tile: the tile's tracks in window order on
-// consecutive tile rows; t_* [kMgMaxTr] and rowmap [kMgCap] (tile row -> input
+// Masks and row map of a packed tile, from its track table (t_start, t_off) and
+// the mask of the rows that start a track: rowmap [kMgCap] (tile row -> input
 // row relative to row0, -1: none) in the wave's LDS; per stream (16 rows) the
 // bits of the rows that start a track (st), of the starts plus the row after
 // the last hit (sb: where a forward pass restarts) and of the track ends (eb).
-__device__ __forceinline__ void mg_tile_meta(unsigned sel, int n, int off, int len, int t, int row0, int lane,
-                                             int *t_start, int *t_len, int *t_off, int *t_id, int *rowmap,
-                                             unsigned &sb0, unsigned &sb1, unsigned &eb0, unsigned &eb1,
-                                             unsigned &st0, unsigned &st1) {
+__device__ __forceinline__ void mg_tile_meta(unsigned long long smask, int n, int row0, int lane, const int *t_start,
+                                             const int *t_off, int *rowmap, unsigned &sb0, unsigned &sb1,
+                                             unsigned &eb0, unsigned &eb1, unsigned &st0, unsigned &st1) {
     constexpr int SP = kMgSP;
-    const bool mine = lane < kMgWin && ((sel >> (lane & 31)) & 1u);
-    const int v = mine ? len : 0;
-    int incl = v;  // inclusive prefix sum of the selected lengths over lanes
-#pragma unroll
-    for (int dd = 1; dd < kMgWin; dd <<= 1) {
-        const int y = __shfl_up(incl, dd);
-        if (lane >= dd) incl += y;
-    }
-    const int rs = incl - v;  // first tile row of this lane's track
-    if (mine) {
-        const int j = __builtin_amdgcn_mbcnt_lo(sel, 0);  // selected tracks before this one
-        t_start[j] = rs;
-        t_len[j] = len;
-        t_off[j] = off;
-        t_id[j] = t + lane;
-    }
-    unsigned long long smask = 0;  // tile rows that start a track
-    for (unsigned m = sel; m; m &= m - 1u) smask |= 1ull << __builtin_amdgcn_readlane(rs, __builtin_ctz(m));
     const unsigned long long valid = (1ull << n) - 1ull;
     const unsigned long long vstart = smask | (1ull << n);
     const unsigned long long emask = ((smask >> 1) | (1ull << (n - 1))) & valid;
@@ -248,31 +248,23 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
     };
     auto slot = [&]() -> const char * { return smem + (q % C::NSLOT) * C::STAGE; };
 
-    const long long gw = (long long)blockIdx.x * C::WAVES + wid;
-    const long long nw = (long long)gridDim.x * C::WAVES;
-    const int g_begin = group_begin(offsets, n_tracks, gw, nw, lane);
-    const int g_end = group_begin(offsets, n_tracks, gw + 1, nw, lane);
+    MgWork wk;
+    wk.begin<C>(smem, smem_lds, offsets, n_tracks, wid, lane);
     const int row0 = offsets[0];
     int errbits = 0;
 
-    int t = g_begin;
-    unsigned taken = 0;
     for (;;) {
-        int n = 0, off = 0, len = 0;
-        const unsigned sel = mg_select(offsets, g_end, row0, x_rows, LLONG_MAX, lane, t, taken, errbits,
-                                       LAST ? states : nullptr, H, n, off, len);
-        const int k = __builtin_popcount(sel);
+        int k, n;
+        unsigned long long smask;
+        if (!wk.next(offsets, row0, x_rows, LLONG_MAX, errbits, LAST ? states : nullptr, H, t_start, k, n, smask)) break;
         const bool work = k > 0;
-        wait_vmcnt<0>();
-        if (!__syncthreads_or(work)) break;  // every wave of the workgroup is done
         copy_stage<C>(stages, (q + C::NSLOT - 1) % S, slot_lds(q + C::NSLOT - 1), wid, lane);
 
         // ---- tile metadata, row map and the input rows as matrix operands
         unsigned sb0 = 0, sb1 = 0, eb0 = 0, eb1 = 0, st0 = 0, st1 = 0;
         FT xa[KIN];
         if (work) {
-            mg_tile_meta(sel, n, off, len, t, row0, lane, t_start, t_len, t_off, t_id, rowmap, sb0, sb1, eb0, eb1,
-                         st0, st1);
+            mg_tile_meta(smask, n, row0, lane, t_start, t_off, rowmap, sb0, sb1, eb0, eb1, st0, st1);
             // A operand: lane (s, i) holds input channels k-step K + s KL .. + KL - 1 of
             // tile row slot_to_hit(i), whose products land in accumulator row i
             const int xr = rowmap[slot_to_hit<SP>(cc)];
@@ -472,6 +464,7 @@ struct BCfg {
     static constexpr int K = 16, KL = 8, EB = 2, FRAG = 64 * KL * EB;
     static constexpr int KIN1 = D / K, KIN2 = 2 * H / K;
     static constexpr int WAVES = 8;  // two per SIMD
+    static constexpr int NPOOL = WAVES / kMgTPP;
     static constexpr int BLOCK1 = round_up(KIN1 * FRAG + 32 * 4, 16);
     static constexpr int BLOCK2 = round_up(KIN2 * FRAG + 32 * 4, 16);
     static constexpr int PARAM_BYTES = (D + 2 * kBbMaxFeat) * 4;
@@ -487,12 +480,12 @@ struct BCfg {
     static constexpr int TB_OFF = 4 * kMgMaxTr * 4 + kMgCap * 4;
     static constexpr int XA_OFF = TB_OFF + kMgCap * ROWB;
     static constexpr int WAVE_BYTES = XA_OFF + KIN1 * FRAG;
-    static constexpr int FLAG_BYTES = 16;  // the tile counter of the last wave with work
-    static constexpr int NSLOT_FIT = (kLdsBytesMax - FLAG_BYTES - WAVES * WAVE_BYTES) / STAGE;
+    static constexpr int NSLOT_FIT = (kLdsBytesMax - WAVES * WAVE_BYTES - NPOOL * kWindowBytes - 16) / STAGE;
     static constexpr int NSLOT = NSLOT_FIT > 5 ? 5 : NSLOT_FIT;
     static constexpr int WAVE0 = NSLOT * STAGE;
-    static constexpr int FLAG_OFF = WAVE0 + WAVES * WAVE_BYTES;
-    static constexpr int LDS_BYTES = FLAG_OFF + FLAG_BYTES;
+    static constexpr int WIN_OFF = WAVE0 + WAVES * WAVE_BYTES;  // the pools' next windows (pool_pack)
+    static constexpr int FLAG_OFF = WIN_OFF + NPOOL * kWindowBytes;  // the tile flag
+    static constexpr int LDS_BYTES = FLAG_OFF + 16;
     static constexpr int L1_STAGES = NCHK, L2_STAGES = 4 * NCHK;
     static_assert(NSLOT >= 2 && KPF >= 1, "stage ring");
     static_assert(kMgCap * kBbUStride * 4 <= KIN1 * FRAG, "features in the operand area");
@@ -565,40 +558,20 @@ void tf_backbone_kernel(const float *__restrict__ feats, int nf, long long n_hit
         }
     };
 
-    const long long gw = (long long)blockIdx.x * C::WAVES + wid;
-    const long long nw = (long long)gridDim.x * C::WAVES;
-    const int g_begin = group_begin(offsets, n_tracks, gw, nw, lane);
-    const int g_end = group_begin(offsets, n_tracks, gw + 1, nw, lane);
+    MgWork wk;
+    wk.begin<C>(smem, smem_lds, offsets, n_tracks, wid, lane);
     const int row0 = offsets[0];
     int errbits = 0;
-    // a wave with a tile writes the tile's number; the workgroup stops at the
-    // first tile that no wave wrote (the next write comes after later barriers)
-    int *tile_flag = reinterpret_cast<int *>(smem + C::FLAG_OFF);
-    if (threadIdx.x == 0) *tile_flag = 0;
-    __syncthreads();
-    int tile_count = 0;
-
-    int t = g_begin;
-    unsigned taken = 0;
     for (;;) {
-        int n = 0, off = 0, len = 0;
-        // (lane values read afresh per tile: held across the tile's layers they
-        // would take registers the last layer's operands need)
-        const unsigned sel =
-            mg_select(offsets, g_end, row0, x_rows, n_hits, fresh_lane(), t, taken, errbits, states, H, n, off, len);
-        const int k = __builtin_popcount(sel);
+        int k, n;
+        unsigned long long smask;
+        if (!wk.next(offsets, row0, x_rows, n_hits, errbits, states, H, t_start, k, n, smask)) break;
         const bool work = k > 0;
-        wait_vmcnt<0>();
-        ++tile_count;
-        if (work && lane == 0) *tile_flag = tile_count;
-        lds_barrier();
-        if (uniform(*tile_flag) != tile_count) break;  // every wave of the workgroup is done
         copy_stage<C>(stages, (q + C::NSLOT - 1) % S, slot_lds(q + C::NSLOT - 1), wid, lane);
 
         unsigned sb0 = 0, sb1 = 0, eb0 = 0, eb1 = 0, st0 = 0, st1 = 0;
         if (work)
-            mg_tile_meta(sel, n, off, len, t, row0, fresh_lane(), t_start, t_len, t_off, t_id, rowmap, sb0, sb1, eb0,
-                         eb1, st0, st1);
+            mg_tile_meta(smask, n, row0, fresh_lane(), t_start, t_off, rowmap, sb0, sb1, eb0, eb1, st0, st1);
 
         // ---- front end: r = b + W f(u) for the hit of column cc (tile row
         // slot_to_hit(cc), the first layer's operand row cc); lane half hh forms

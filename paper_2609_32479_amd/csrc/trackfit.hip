@@ -94,6 +94,15 @@ struct KCfg {
     // its per-tile register arrays on every path, so that nothing is held (or
     // spilled) across tiles.
     static constexpr bool TIGHT = WAVES > 4;
+    // tiles of a round (one per wave or pair), packed from pools of TPP tiles each:
+    // one pool per workgroup where a round is long (fp32 and d = 256, 200 us and
+    // more), smaller ones where the packing of a whole round would show (d <= 128,
+    // 60 us a round: pools of 12, 4 tiles +3.6, +0.6 % on full tiles; 64-row pairs,
+    // pools of 6, 3, 2 tiles +1.5, +0.7, +0.3 % on 64-hit tracks, which gain nothing)
+    static constexpr int TPB = PAIR ? WAVES / 2 : WAVES;
+    static constexpr int TPP = PAIR ? 2 : (HALF && D <= 128) ? 4 : WAVES;
+    static constexpr int NPOOL = TPB / TPP;
+    static_assert(NPOOL * TPP == TPB, "pools");
     // wave-private LDS: [f; b] buffer, aliased by the pooling scratch
     // [f; b] buffer: fp32 slot-major with a padded row; 16-bit channel-major
     // (row k = channel k of the chunk's [f; b], CAP slots, swizzled by fb_off)
@@ -105,7 +114,7 @@ struct KCfg {
     static constexpr int EMB_BYTES = D * 16;
     // PAIR: per wave pair, the two scan hand-over rows (64 floats each) and their flags
     static constexpr int PX_BYTES = PAIR ? (WAVES / 2) * (2 * 64 * 4 + 16) : 0;
-    static constexpr int RING_BYTES = kLdsBytesMax - EMB_BYTES - WAVES * WAVE_BYTES - 16 - PX_BYTES;  // for the stage ring
+    static constexpr int RING_BYTES = kLdsBytesMax - EMB_BYTES - WAVES * WAVE_BYTES - NPOOL * kWindowBytes - 16 - PX_BYTES;  // for the stage ring
     // Weight stages, all padded to STAGE bytes.  A chunk's input and output
     // projections share one stage (one barrier per chunk) when two such stages
     // fit in the ring; otherwise each has its own.
@@ -138,7 +147,8 @@ struct KCfg {
     static constexpr int NSLOT = NSLOT_FIT > 4 ? 4 : NSLOT_FIT;
     static_assert(NSLOT >= 2, "stage ring");
     static constexpr int WAVE0 = SLOT0 + NSLOT * STAGE;
-    static constexpr int FLAG_OFF = WAVE0 + WAVES * WAVE_BYTES;  // the tile flag (see the kernel)
+    static constexpr int WIN_OFF = WAVE0 + WAVES * WAVE_BYTES;  // the next window's offsets
+    static constexpr int FLAG_OFF = WIN_OFF + NPOOL * kWindowBytes;  // the tile flag (see the kernel)
     static constexpr int PX_OFF = FLAG_OFF + 16;
     static constexpr int LDS_BYTES = PX_OFF + PX_BYTES;
     static_assert(!PAIR || (HT == 1 && PIPE && MERGE && HEAD16 && WAVES % 2 == 0), "paired tiles");
@@ -369,12 +379,6 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
     auto slot_lds = [&](int q) -> unsigned { return smem_lds + C::SLOT0 + (q % C::NSLOT) * C::STAGE; };
 #pragma unroll
     for (int q = 0; q < C::NSLOT - 1; ++q) copy_stage<C>(P.stages, q % S, slot_lds(q), wid, lane);
-    // The tile flag: at the start of its t-th tile every wave that has a tile
-    // writes t, so the workgroup stops when after the barrier it does not read
-    // t.  (No wave writes t + 1 before every wave has read it: each tile has
-    // barriers of its own.)
-    int *tile_flag = reinterpret_cast<int *>(smem + C::FLAG_OFF);
-    if (threadIdx.x == 0) *tile_flag = 0;
     if constexpr (C::PAIR) {
         if (threadIdx.x < C::WAVES / 2) {
             int *f = reinterpret_cast<int *>(smem + C::PX_OFF + threadIdx.x * (2 * 64 * 4 + 16) + 2 * 64 * 4);
@@ -382,8 +386,35 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
             f[1] = 0;
         }
     }
-    lds_barrier();  // the flag and the embedding table are in place
+    // This wave's pool: a contiguous range of tracks balanced by hit rows, shared
+    // by TPP waves (or pairs) of the workgroup, whose tiles of a round all of them
+    // pack alike (pool_pack); this wave takes tile `me`.
+    const int tile_no = C::PAIR ? pi : wid;
+    // (the pools' first tiles go to waves of different SIMDs, which matters when a
+    // round has few tiles: 500 tracks, 52 -> 37 us)
+    const int pid = uniform(tile_no / C::TPP), me = uniform((tile_no + pid) % C::TPP);
+    const bool lead = me == 0 && pb == 0;  // the wave that reads ahead and reports for the pool
+    TrackPool pool;
+    {
+        const long long g = (long long)blockIdx.x * C::NPOOL + pid, ng = (long long)gridDim.x * C::NPOOL;
+        pool.t = uniform(group_begin(offsets, n_tracks, g, ng, lane));
+        pool.end = uniform(group_begin(offsets, n_tracks, g + 1, ng, lane));
+        pool.taken = 0;
+    }
+    const unsigned win_lds = smem_lds + C::WIN_OFF + pid * kWindowBytes;
+    const int *win = reinterpret_cast<const int *>(smem + C::WIN_OFF + pid * kWindowBytes);
+    if (lead) {
+        prefetch_window(offsets, pool, win_lds, lane);
+        wait_vmcnt<0>();
+    }
+    // The tile flag: at the start of its t-th tile every wave that has a tile
+    // writes t, so the workgroup stops when after the barrier it does not read
+    // t.  (No wave writes t + 1 before every wave has read it: each tile has
+    // barriers of its own.)
+    int *tile_flag = reinterpret_cast<int *>(smem + C::FLAG_OFF);
+    if (threadIdx.x == 0) *tile_flag = 0;
     int tile_count = 0;
+    lds_barrier();  // the embedding table, the flag, the windows (and the pairs' flags) are in place
 
     // Stage q (counted across tiles; a tile iteration takes S stages) lives in
     // slot q % NSLOT.  At the end of stage q every wave waits for its share of
@@ -429,78 +460,33 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
         return buf[lane];
     };
 
-    // Contiguous group of tracks for this wave, balanced by hit rows.
-    // (a pair shares one group)
-    constexpr int GPB = C::PAIR ? C::WAVES / 2 : C::WAVES;  // groups per workgroup
-    const long long gw = (long long)blockIdx.x * GPB + (C::PAIR ? pi : wid);
-    const long long nw = (long long)gridDim.x * GPB;
-    const int g_begin = group_begin(offsets, n_tracks, gw, nw, lane);
-    const int g_end = group_begin(offsets, n_tracks, gw + 1, nw, lane);
-
-
-    // Tiles are packed from a window of the wave's tracks: the first track not
-    // yet fitted (t) and the WIN - 1 after it, in track order; bit i of `taken`
-    // marks track t + i as fitted into an earlier tile (or refused).  The first
-    // track of the window always goes in, so every tile makes progress, and a
-    // track's result does not depend on the tile it lands in.
-    constexpr int WIN = 32;
-    int t = g_begin;
-    unsigned taken = 0;
     for (;;) {
-        int k = 0, n = 0;      // tracks and hit rows of the tile
-        unsigned sel = 0;      // window tracks of the tile
-        int off = 0, len = 0;  // lane i < WIN: first hit row and length of track t + i
-        while (t < g_end) {
-            // slide the window past its leading fitted tracks
-            const int sh = taken == ~0u ? WIN : __builtin_ctz(~taken);
-            taken = sh == WIN ? 0u : taken >> sh;
-            t += sh;
-            if (t >= g_end) break;
-            const int idx = t + lane;
-            off = 0;
-            if (lane <= WIN && idx <= g_end) off = offsets[idx];
-            const int nxt = __shfl_down(off, 1);
-            len = nxt - off;
-            const bool fresh = lane < WIN && idx < g_end && !((taken >> (lane & 31)) & 1u);
-            // tracks that cannot be fitted: rows outside [0, n_hits), an end
-            // before the start, no hits, or more hits than a tile holds
-            const bool bad = off < 0 || nxt < off || (long long)nxt > n_hits_total;
-            const bool empty = !bad && len == 0;
-            const bool too_long = !bad && len > C::TCAP;
-            const unsigned long long bad_m = __ballot(fresh && bad);
-            const unsigned long long empty_m = __ballot(fresh && empty);
-            const unsigned long long long_m = __ballot(fresh && too_long);
-            if (bad_m | empty_m | long_m) {
+        int k, n;                  // tracks and hit rows of the tile
+        unsigned long long smask;  // tile rows that start a track
+        pool_pack<C::TCAP, TMAXTR, C::TPP>(
+            offsets, win, pool, 0, n_hits_total, me, C::TIGHT ? fresh_lane() : lane, t_start, k, n, smask,
+            [&](unsigned long long bad_m, unsigned long long empty_m, unsigned long long long_m, int idx) {
+                if (!lead) return;
                 errbits |= (bad_m ? TF_DEVERR_BAD_OFFSETS : 0) | (empty_m ? TF_DEVERR_EMPTY_TRACK : 0) |
                            (long_m ? TF_DEVERR_TOO_LONG : 0);
-                if (!FRONT && fresh && (bad || empty || too_long)) {
+                if (!FRONT && (((bad_m | empty_m | long_m) >> (C::TIGHT ? fresh_lane() : lane)) & 1ull)) {
                     // (a NaN made here, so that the compiler does not keep one across tiles)
                     float qnan;
                     asm volatile("v_mov_b32 %0, 0x7fc00000" : "=v"(qnan));
 #pragma unroll
                     for (int e = 0; e < OUTW; ++e) out[(size_t)idx * OUTW + e] = qnan;
                 }
-                taken |= unsigned(bad_m | empty_m | long_m);
-            }
-            // first-fit in window order (the pair search costs this kernel more per
-            // tile than it saves)
-            const unsigned cand = unsigned(__ballot(fresh && !bad && !empty && !too_long));
-            if (cand) {
-                sel = pack_tile<C::TCAP, TMAXTR, false>(cand, len, lane, n);
-                k = __builtin_popcount(sel);
-                taken |= sel;
-                break;
-            }
-        }
+            });
         const bool work = k > 0;
-        wait_vmcnt<0>();                     // stages q .. q + NSLOT - 2 are in LDS
+        wait_vmcnt<0>();  // stages q .. q + NSLOT - 2 are in LDS
         ++tile_count;
-        if (work && lane == 0) *tile_flag = tile_count;
+        if (work && (C::TIGHT ? fresh_lane() : lane) == 0) *tile_flag = tile_count;
         lds_barrier();
-        if (uniform(*tile_flag) != tile_count) break;  // every wave of the workgroup is done
+        if (uniform(*tile_flag) != tile_count) break;  // every pool of the workgroup is empty
+        if (lead) prefetch_window(offsets, pool, win_lds, C::TIGHT ? fresh_lane() : lane);
         copy_stage<C>(P.stages, (q + C::NSLOT - 1) % S, slot_lds(q + C::NSLOT - 1), wid, lane);
 
-        // ---- tile metadata: the tile's tracks in window order, on consecutive
+        // ---- tile metadata: the tile's tracks on consecutive
         // tile rows; per stream, in register order (slot_to_row), the rows whose
         // coefficient the ascending pass zeroes (su0: track starts of stream 0,
         // forward; su1: track ends of stream 1, reverse) and the descending pass
@@ -518,25 +504,6 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     for (int q = 0; q < 16; ++q) r[m][nt][q] = 0.f;
         }
         if (work) {
-            const int ln = C::TIGHT ? fresh_lane() : lane;
-            const bool mine = ln < WIN && ((sel >> (ln & 31)) & 1u);
-            const int v = mine ? len : 0;
-            int incl = v;  // inclusive prefix sum of the selected lengths over lanes
-#pragma unroll
-            for (int d = 1; d < WIN; d <<= 1) {
-                const int y = __shfl_up(incl, d);
-                if (ln >= d) incl += y;
-            }
-            const int row0 = incl - v;
-            if (mine) {
-                const int j = __builtin_amdgcn_mbcnt_lo(sel, 0);  // selected tracks before this one
-                t_start[j] = row0;
-                t_len[j] = len;
-                t_off[j] = off;
-                t_id[j] = t + ln;
-            }
-            unsigned long long smask = 0;  // tile rows that start a track
-            for (unsigned m = sel; m; m &= m - 1u) smask |= 1ull << __builtin_amdgcn_readlane(row0, __builtin_ctz(m));
             const unsigned long long valid = n >= 64 ? ~0ull : ((1ull << n) - 1);
             const unsigned long long vstart = smask | (n < 64 ? (1ull << n) : 0ull);
             const unsigned long long emask = ((smask >> 1) | (1ull << (n - 1))) & valid;

@@ -18,7 +18,7 @@ def _call(w):
     if w.arch == "mingru":
         M = tf.MinGRU(ts.make_mingru_weights(w), w.n_layers, w.d_model, w.hidden, mode, w.n_features)
         return lambda h, o: M.states(h, o)
-    W = tf.Weights(ts.make_weights(w), w.n_layers, w.d_model, mode, max_hits=w.len_max)
+    W = tf.Weights(ts.make_weights(w), w.n_layers, w.d_model, mode, max_hits=64 if w.len_max > 32 else 32)
     return lambda h, o: tf.fit_tracks(h, o, W)
 
 
@@ -39,3 +39,27 @@ def test_batch_sizes_match_one_large_call(name):
     for first, m in ((0, 1), (7, 2), (0, 13), (100, 255), (3, 256), (11, 257), (500, 1025)):
         part = call(h, o[first:first + m + 1].contiguous()).cpu()
         assert torch.equal(part, whole[first:first + m]), (name, first, m)
+
+
+@pytest.mark.parametrize("lens", [(1, 1), (1, 3), (16, 16), (17, 17), (32, 32), (1, 34), (0, 40)])
+@pytest.mark.parametrize("name", ["deploy_d128x4_bf16_8m", "mingru2_h64_tiny_d32_fp32"])
+def test_tiles_of_any_lengths_match_single_tracks(name, lens):
+    """Tiles packed from windows of 64 tracks: one full track a tile, 16 one-hit
+    tracks a tile (windows used up within a round), tracks that never share a
+    tile, refused tracks in between.  Sampled tracks must give the bits of a call
+    of their own; every refused track gives NaN and no other does."""
+    w = ts.workload(name)
+    n = 9000 if lens[1] <= 3 else 3000
+    rng = np.random.default_rng(17)
+    lengths = rng.integers(lens[0], lens[1] + 1, n)
+    offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    hits = (rng.uniform(-1, 1, (offs[-1], 3)) * [1000, 1000, 3000]).astype(np.float32)
+    h, o = torch.from_numpy(hits).cuda(), torch.from_numpy(offs).cuda()
+    call = _call(w)
+    whole = call(h, o).cpu()
+    good = torch.from_numpy((lengths > 0) & (lengths <= 32))
+    assert torch.equal(torch.isfinite(whole).all(dim=1), good)
+    assert torch.isnan(whole[~good]).all()
+    for i in rng.choice(n, 40, replace=False):
+        one = call(h, o[i:i + 2].contiguous()).cpu()
+        assert torch.equal(one.isnan(), whole[i:i + 1].isnan()) and torch.equal(one.nan_to_num(), whole[i:i + 1].nan_to_num())
