@@ -51,22 +51,27 @@ constexpr int kMgTPP = 4;     // waves that share a pool of tracks (pool_pack)
 template <int OP, int DIN>
 struct MCfg {
     static constexpr bool HALF = OP != OP_F32;
-    static constexpr int K = HALF ? 16 : 2;  // reduction depth of one product
+    static constexpr int K = 16;             // reduction depth of one product
     static constexpr int KL = K / 2;         // operand values per lane per k-step
     static constexpr int KIN = DIN / K;      // k-steps over the layer's input
-    static constexpr int EB = HALF ? 2 : 4;
-    static constexpr int FRAG = 64 * KL * EB;
-    // 16-bit operands: two waves per SIMD (256 registers: the input operands
-    // take DIN / 4); fp32 operands: one (DIN / 2 of the 512)
-    static constexpr int WAVES = HALF ? 8 : 4;
+    static constexpr int EB = HALF ? 2 : 4;  // bytes of a row element
+    static constexpr int FRAG = 64 * KL * (HALF ? 2 : 6);
+    // Two waves per SIMD (256 registers: the input operands take DIN / 4, or 3 / 4 of
+    // DIN in fp32), one (512) for the fp32 layers of input 384.
+    static constexpr int WAVES = HALF || DIN <= 128 ? 8 : 4;
     static constexpr int NPOOL = WAVES / kMgTPP;
-    // one weight block: a 32-row slice of the candidate or gate rows, then its 32 biases
-    static constexpr int BLOCK = round_up(KIN * FRAG + 32 * 4, 16);
+    // one weight block: a 32-row slice of the candidate or gate rows in SPB stages of
+    // KPS k-steps each (two where the fp32 parts of a block would take 72 KB), each
+    // with its 32 biases behind
+    static constexpr int SPB = !HALF && DIN > 256 ? 2 : 1;
+    static constexpr int KPS = KIN / SPB;
+    static_assert(KPS * SPB == KIN, "k-steps per stage");
+    static constexpr int BLOCK = round_up(KPS * FRAG + 32 * 4, 16);
     // a stage holds one block, or both blocks of a chunk and direction when two
     // slots of that size still leave room for a ring of at least three
-    static constexpr bool MERGE = 3 * round_up(2 * BLOCK, kCopyBytes) + WAVES * (4 * kMgMaxTr * 4 + kMgCap * 4 + kMgCap * (32 * EB + 16)) + NPOOL * kWindowBytes + 16 <= kLdsBytesMax;
+    static constexpr bool MERGE = SPB == 1 && 3 * round_up(2 * BLOCK, kCopyBytes) + WAVES * (4 * kMgMaxTr * 4 + kMgCap * 4 + kMgCap * (32 * EB + 16)) + NPOOL * kWindowBytes + 16 <= kLdsBytesMax;
     static constexpr int STAGE = round_up((MERGE ? 2 : 1) * BLOCK, kCopyBytes);
-    static constexpr int SPC = MERGE ? 1 : 2;  // stages per chunk and direction
+    static constexpr int SPC = MERGE ? 1 : 2 * SPB;  // stages per chunk and direction
     static constexpr int COPIES = STAGE / kCopyBytes;
     static constexpr int LPW = (COPIES + WAVES - 1) / WAVES;
     // wave-private LDS: track table and row map, then the output transpose tile
@@ -270,10 +275,19 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
             const int xr = rowmap[slot_to_hit<SP>(cc)];
 #pragma unroll
             for (int ks = 0; ks < KIN; ++ks) {
-                if (xr >= 0)
-                    xa[ks] = *reinterpret_cast<const FT *>(X + (size_t)xr * DIN + ks * K + hh * KL);
-                else
+                if (xr >= 0) {
+                    const FE *xp = X + (size_t)xr * DIN + ks * K + hh * KL;
+                    if constexpr (C::HALF) {
+                        xa[ks] = *reinterpret_cast<const FT *>(xp);
+                    } else {
+                        const f32x4 v0 = *reinterpret_cast<const f32x4 *>(xp);
+                        const f32x4 v1 = *reinterpret_cast<const f32x4 *>(xp + 4);
+                        const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                        xa[ks] = F::pack(v);
+                    }
+                } else {
                     xa[ks] = FT{};
+                }
             }
         }
 
@@ -307,38 +321,51 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
             }
         };
 
+        // acc = X W^T of the weight block that starts in the current stage at `off`
+        // (its later stages taken as they come), without the bias; leaves the ring at the
+        // block's last stage.  Two accumulators where one wave has the SIMD to itself:
+        // a chain of dependent products runs at 44 cycles each instead of 32.
+        auto products = [&](f32x16 &acc, int off) {
+            f32x16 odd;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = odd[i] = 0.f;
+#pragma unroll
+            for (int sp = 0; sp < C::SPB; ++sp) {
+                if (sp > 0) advance(false);
+                if (work) {
+                    const FT *wf = reinterpret_cast<const FT *>(slot() + off);
+                    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                    for (int kl = 0; kl < C::KPS; ++kl) {
+                        const int ks = sp * C::KPS + kl;
+                        if (C::WAVES == 4 && (kl & 1))
+                            odd = F::mma(xa[ks], wf[kl * 64 + lane], odd);
+                        else
+                            acc = F::mma(xa[ks], wf[kl * 64 + lane], acc);
+                    }
+                    __builtin_amdgcn_s_setprio(0);
+                }
+            }
+            if constexpr (C::WAVES == 4) acc += odd;
+        };
+
         // ---- chunks of 32 hidden channels, forward then reverse direction
         for (int ch = 0; ch < NCHK; ++ch) {
 #pragma unroll
             for (int dir = 0; dir < 2; ++dir) {
-                f32x16 ax;
-                if (work) {
-                    // candidate block: rows dir 2H + 32 ch + cc of the layer's weights
-                    const FT *wf = reinterpret_cast<const FT *>(slot());
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) ax[i] = 0.f;
-                    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-                    for (int ks = 0; ks < KIN; ++ks) ax = F::mma(xa[ks], wf[ks * 64 + lane], ax);
-                    __builtin_amdgcn_s_setprio(0);
-                    ax += reinterpret_cast<const float *>(slot() + KIN * C::FRAG)[cc];
-                }
+                // candidate block: rows dir 2H + 32 ch + cc of the layer's weights
+                f32x16 ax, gx;
+                products(ax, 0);
+                if (work) ax += reinterpret_cast<const float *>(slot() + C::KPS * C::FRAG)[cc];
                 if constexpr (!C::MERGE) advance(false);
                 flush();  // the previous block's outputs
-                // the gate block: the next stage, or the second block of this one
-                const char *gsl = slot() + (C::MERGE ? C::BLOCK : 0);
+                // the gate block: the next stage, or the second block of this one; rows
+                // dir 2H + H + 32 ch + cc; bias pre-scaled by -log2(e) in the 16-bit modes
+                // (exp2 below)
+                constexpr int GOFF = C::MERGE ? C::BLOCK : 0;
+                products(gx, GOFF);
                 if (work) {
-                    // gate block: rows dir 2H + H + 32 ch + cc; bias pre-scaled by -log2(e)
-                    // in the 16-bit modes (exp2 below)
-                    const FT *wf = reinterpret_cast<const FT *>(gsl);
-                    f32x16 gx;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) gx[i] = 0.f;
-                    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-                    for (int ks = 0; ks < KIN; ++ks) gx = F::mma(xa[ks], wf[ks * 64 + lane], gx);
-                    __builtin_amdgcn_s_setprio(0);
-                    const float bgv = reinterpret_cast<const float *>(gsl + KIN * C::FRAG)[cc];
+                    const float bgv = reinterpret_cast<const float *>(slot() + GOFF + C::KPS * C::FRAG)[cc];
                     float AX[SP], CF[SP];
 #pragma unroll
                     for (int i = 0; i < SP; ++i) {
@@ -801,14 +828,15 @@ hipError_t launch_backbone(const float *feats, int nf, long long n_hits, long lo
     return hipGetLastError();
 }
 
-// Stage geometry of a layer for the host: bytes per stage, per block, and
-// whether a chunk's candidate and gate blocks share a stage.
+// Stage geometry of a layer for the host: bytes per stage, per block (or part of
+// one), whether a chunk's candidate and gate blocks share a stage, and the stages
+// per block.
 struct MGeom {
-    int stage, block, merge;
+    int stage, block, merge, spb;
 };
 template <int OP, int DIN>
 MGeom stage_bytes() {
-    return {MCfg<OP, DIN>::STAGE, MCfg<OP, DIN>::BLOCK, MCfg<OP, DIN>::MERGE ? 1 : 0};
+    return {MCfg<OP, DIN>::STAGE, MCfg<OP, DIN>::BLOCK, MCfg<OP, DIN>::MERGE ? 1 : 0, MCfg<OP, DIN>::SPB};
 }
 
 int op_of(int32_t dtype) { return dtype == TF_BF16 ? OP_BF16 : dtype == TF_BF16_F16ACT ? OP_F16 : OP_F32; }
@@ -914,7 +942,7 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
     if (n_floats != tf_mingru_blob_size(cfg)) return TF_EINVAL;
     const int op = op_of(cfg->dtype);
     const bool half = op != OP_F32, bf = op == OP_BF16;
-    const int K = half ? 16 : 2, KL = K / 2;
+    const int K = 16, KL = K / 2;
 
     tf_mingru *h = new (std::nothrow) tf_mingru;
     if (!h) return TF_ENOMEM;
@@ -940,16 +968,14 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
         }
     }
     // layer stages: for each 32-channel chunk and direction, the candidate block then
-    // the gate block; lane (s, c) value e of k-step ks holds W[row 32 ch + c of the
-    // block][column ks K + s KL + e]; then the block's 32 biases (the gate's times
-    // -log2(e) for the 16-bit modes)
+    // the gate block
     std::vector<size_t> loff(L);
     size_t total = 0;
     for (int l = 0; l < L; ++l) {
         const int din = l == 0 ? d : 2 * H;
         loff[l] = total;
         const MGeom g = stage_bytes_of(op, din);
-        total += (size_t)(g.merge ? 2 : 4) * (H / 32) * g.stage;
+        total += (size_t)(g.merge ? 2 : 4 * g.spb) * (H / 32) * g.stage;
     }
     const size_t err_off = total;
     total += 256;
@@ -962,30 +988,33 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
     const size_t bb_off = (total + 255) & ~size_t(255);
     if (fusable) total = bb_off + (size_t)(bb_nfs + BC::L1_STAGES + BC::L2_STAGES) * BC::STAGE;
     std::vector<unsigned char> hb(total, 0);
-    auto put_elem = [&](unsigned char *sp, size_t i, float v) {
-        if (half) {
-            const uint16_t bb = bits16(v, bf);
-            std::memcpy(sp + 2 * i, &bb, 2);
-        } else {
-            std::memcpy(sp + 4 * i, &v, 4);
+    // value e of the lane whose eight values start at element i (fp32: the three
+    // bf16 parts of all eight one after the other)
+    auto put_elem = [&](unsigned char *sp, size_t i, int e, float v) {
+        for (int part = 0; part < (half ? 1 : 3); ++part) {
+            const uint16_t bb = half ? bits16(v, bf) : bf16_part(v, part);
+            std::memcpy(sp + 2 * (half ? i + e : 3 * i + 8 * part + e), &bb, 2);
         }
     };
-    // one weight block: lane (s, c) value e of k-step ks holds W[row rbase + c][column
-    // ks K + s KL + e]; then the block's 32 biases (the gate's times -log2(e) for the
-    // 16-bit modes)
-    auto put_block = [&](unsigned char *sp, const float *W, const float *b, int din, int rbase, bool gate_part) {
-        const int KIN = din / K;
-        for (int ks = 0; ks < KIN; ++ks)
+    // k-steps k0 .. k0 + nk - 1 of one weight block: lane (s, c) value e of k-step ks
+    // holds W[row rbase + c][column ks K + s KL + e]; then the block's 32 biases (the
+    // gate's times -log2(e) for the 16-bit modes)
+    auto put_part = [&](unsigned char *sp, const float *W, const float *b, int din, int rbase, bool gate_part, int k0,
+                        int nk) {
+        for (int kl = 0; kl < nk; ++kl)
             for (int lane = 0; lane < 64; ++lane)
                 for (int e = 0; e < KL; ++e)
-                    put_elem(sp, ((size_t)ks * 64 + lane) * KL + e,
-                             W[(size_t)(rbase + lane % 32) * din + ks * K + (lane / 32) * KL + e]);
-        unsigned char *bp = sp + (size_t)KIN * 64 * KL * (half ? 2 : 4);
+                    put_elem(sp, ((size_t)kl * 64 + lane) * KL, e,
+                             W[(size_t)(rbase + lane % 32) * din + (k0 + kl) * K + (lane / 32) * KL + e]);
+        unsigned char *bp = sp + (size_t)nk * 64 * KL * (half ? 2 : 6);
         for (int c = 0; c < 32; ++c) {
             float bv = b[rbase + c];
             if (half && gate_part) bv = (float)(-1.4426950408889634 * (double)bv);
             std::memcpy(bp + 4 * c, &bv, 4);
         }
+    };
+    auto put_block = [&](unsigned char *sp, const float *W, const float *b, int din, int rbase, bool gate_part) {
+        put_part(sp, W, b, din, rbase, gate_part, 0, din / K);
     };
     const float *lw = blob + front_floats(d, nf);
     for (int l = 0; l < L; ++l) {
@@ -1002,8 +1031,10 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
             for (int dir = 0; dir < 2; ++dir)
                 for (int part = 0; part < 2; ++part) {
                     const int rbase = dir * 2 * H + part * H + 32 * ch;
-                    put_block(dst, W, b, din, rbase, part == 1);
-                    dst += (g.merge && part == 0) ? g.block : (g.merge ? g.stage - g.block : g.stage);
+                    for (int sp = 0; sp < g.spb; ++sp) {
+                        put_part(dst, W, b, din, rbase, part == 1, sp * din / K / g.spb, din / K / g.spb);
+                        dst += (g.merge && part == 0) ? g.block : (g.merge ? g.stage - g.block : g.stage);
+                    }
                     if (fusable) {
                         put_block(fdst + (l == 0 ? (2 * dir + part) * BC::BLOCK1 : 0), W, b, din, rbase, part == 1);
                         fdst += l == 0 ? (dir == 1 && part == 1 ? BC::STAGE : 0) : BC::STAGE;
@@ -1026,7 +1057,7 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
                     for (int lane = 0; lane < 64; ++lane)
                         for (int e = 0; e < 8; ++e) {
                             const size_t col = (size_t)(js * BC::KPF + kl) * 16 + (lane / 32) * 8 + e;
-                            put_elem(sp, ((size_t)(kl * 4 + m) * 64 + lane) * 8 + e,
+                            put_elem(sp, ((size_t)(kl * 4 + m) * 64 + lane) * 8, e,
                                      fW[(size_t)(32 * m + bb_front_channel(lane % 32)) * KF32 + col]);
                         }
         }

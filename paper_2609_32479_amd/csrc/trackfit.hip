@@ -22,8 +22,8 @@
 //    compute.  Weights are stored in the device already in per-lane fragment
 //    order, so every copy and every operand read is a contiguous 1 KiB per
 //    wave.
-//  * Projections run on 32x32 matrix cores: v_mfma_f32_32x32x16_{bf16,f16}
-//    for the 16-bit modes, v_mfma_f32_32x32x2_f32 for the fp32 model.  The
+//  * Projections run on 32x32 matrix cores, v_mfma_f32_32x32x16_{bf16,f16}; the
+//    fp32 model's operands are split into three bf16 parts each.  The
 //    residual stream is held transposed (channels on MFMA rows, hits on
 //    columns), which is exactly the operand layout of the input projection,
 //    so the norm output feeds the matrix core without any data movement.
@@ -74,19 +74,19 @@ struct KCfg {
     static constexpr int TMAXTR = PAIR ? 32 : MAXTR;  // tracks of a tile
     static constexpr int MT = D / 32;            // 32-channel blocks
     static constexpr int NCH = D / 32;           // chunks of the scan / output projection
-    static constexpr int K = HALF ? 16 : 2;      // MFMA reduction depth
+    static constexpr int K = 16;                 // MFMA reduction depth
     static constexpr int KL = K / 2;             // operand values per lane per k-step
     static constexpr int KS1 = D / K;            // k-steps over d
     static constexpr int KS2 = 64 / K;           // k-steps over one chunk of [f; b]
     static constexpr int RPK = 16 / KL;          // k-steps per 16 accumulator rows
     static constexpr int KPB = 32 / K;           // k-steps per 32-channel block
-    static constexpr int EB = HALF ? 2 : 4;      // operand element bytes
-    static constexpr int FRAG = 64 * KL * EB;    // one wave-wide operand fragment
-    // waves per workgroup (three per SIMD for the 16-bit d <= 128 kernels; two
-    // where the registers of two waves fit: d = 256 with fp16 activations
-    // (-26 % time per launch against one wave) and the fp32 d = 128 model
-    // (-10 %); one for the rest)
-    static constexpr int WAVES = (HALF && HT == 1 && D <= 128)                                   ? 12
+    static constexpr int EB = HALF ? 2 : 4;      // element bytes of the [f; b] buffer
+    static constexpr int FRAG = 64 * KL * (HALF ? 2 : 6);  // one wave-wide operand fragment
+    // waves per workgroup (three per SIMD for the 16-bit d <= 128 kernels and the
+    // fp32 d <= 64 ones; two where the registers of two waves fit: d = 256 with fp16
+    // activations (-26 % time per launch against one wave) and the fp32 d = 128
+    // model (-10 %); one for the rest)
+    static constexpr int WAVES = (HT == 1 && (HALF ? D <= 128 : D <= 64))                           ? 12
                                  : (HT == 1 && ((OP == OP_F16 && D == 256) || (!HALF && D == 128))) ? 8
                                                                                                       : 4;
     // Three waves per SIMD leave 168 registers a wave, two 256.  Under that budget the
@@ -106,7 +106,7 @@ struct KCfg {
     // wave-private LDS: [f; b] buffer, aliased by the pooling scratch
     // [f; b] buffer: fp32 slot-major with a padded row; 16-bit channel-major
     // (row k = channel k of the chunk's [f; b], CAP slots, swizzled by fb_off)
-    static constexpr int FBS = HALF ? CAP : 65;  // row stride of [f; b] (elements)
+    static constexpr int FBS = HALF ? CAP : 68;  // row stride of [f; b] (elements)
     static constexpr int STS = 33;               // row stride of the pooling scratch (floats)
     static constexpr int FB_BYTES = HALF ? (64 * CAP + (HT_ == 1 ? 64 : 0)) * EB : CAP * FBS * EB;
     static constexpr int POOL_BYTES = CAP * STS * 4 + MAXTR * STS * 4;
@@ -118,16 +118,22 @@ struct KCfg {
     // Weight stages, all padded to STAGE bytes.  A chunk's input and output
     // projections share one stage (one barrier per chunk) when two such stages
     // fit in the ring; otherwise each has its own.
-    static constexpr int G1_FR = 2 * KS1;        // candidate + gate fragments of a chunk
-    static constexpr int G2_FR = MT * KS2;       // output-projection fragments of a chunk
-    static constexpr int G1_BYTES = G1_FR * FRAG + 64 * 4;  // + bx[32], bg[32]
+    // fp32: the fragments are three times as large, so the gate's and the
+    // candidate's products of a chunk have a stage each, and the output
+    // projection one per half of its channel blocks.
+    static constexpr int NIN = HALF ? 1 : 2;                 // stages of a chunk's input projection
+    static constexpr int NOUT = HALF || MT < 2 ? 1 : 2;      // stages of its output projection
+    static constexpr int MPO = MT / NOUT;                    // channel blocks of such a stage
+    static constexpr int G1_FR = 2 / NIN * KS1;  // (candidate +) gate fragments of a stage
+    static constexpr int G2_FR = MPO * KS2;      // output-projection fragments of a stage
+    static constexpr int G1_BYTES = G1_FR * FRAG + 64 * 4;  // + bx[32], bg[32] (fp32: one of them)
     static constexpr int G2_BYTES = G2_FR * FRAG + D * 4;   // + bout[D]
     static constexpr int MERGED_STAGE = round_up(round_up(G1_BYTES, 16) + G2_BYTES, kCopyBytes);
     // PIPE (16-bit, d <= 128): pipelined layers, where chunk c runs its input
     // projection and then its gate interleaved with the output projection of
     // chunk c - 1; merged, those two share a stage.
     static constexpr bool PIPE = HALF && D <= 128;
-    static constexpr bool MERGE = RING_BYTES / MERGED_STAGE >= 2;
+    static constexpr bool MERGE = HALF && RING_BYTES / MERGED_STAGE >= 2;
     static constexpr int STAGE = MERGE ? MERGED_STAGE : round_up(cmax(G1_BYTES, G2_BYTES), kCopyBytes);
     static constexpr int G2_OFF = MERGE ? round_up(G1_BYTES, 16) : 0;  // output projection in its stage
     static constexpr int KSPS_RAW = (STAGE - D * 4) / (MT * FRAG);   // head-1 k-steps per stage
@@ -583,7 +589,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
             // projection), formed in registers: sin or cos of pi 2^s u_f
             const float *us = stage;
             const int kf = 32 * P.n_feat / K;  // k-steps of the projection
-            FT cnext[HT];  // 16-bit: the cosines that the k-step after an even one takes
+            FT cnext[HT];  // the cosines that the k-step after an even one takes
 #pragma unroll
             for (int nt = 0; nt < HT; ++nt) cnext[nt] = FT{};
             for (int js = 0; js < P.n_fstages; ++js) {
@@ -626,11 +632,17 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                                 }
                                 cnext[nt] = F::pack(cv);
                             } else {
-                                // one feature per lane and k-step; the library's sinpi/cospi
-                                // reduce the exact argument 2^s u exactly
-                                const int k = ks * K + hh;
-                                const float x = ldexpf(us[sl * kUStride + (k >> 5)], k & 15);
-                                v[0] = ((k >> 4) & 1) ? cospif(x) : sinpif(x);
+                                // the library's sinpi and cospi reduce the exact argument 2^s u
+                                // exactly; here too the even k-step forms the cosines with its sines
+                                if (ks & 1) {
+                                    bv[nt] = cnext[nt];
+                                    continue;
+                                }
+                                const float u = us[sl * kUStride + (ks >> 1)] * (hh ? 256.0f : 1.0f);
+                                float cv[8];
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) sincospif(u * (float)(1 << e), &v[e], &cv[e]);
+                                cnext[nt] = F::pack(cv);
                             }
                             bv[nt] = F::pack(v);
                         }
@@ -685,32 +697,39 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
             for (int ch = 0; ch < NCH; ++ch) {
                 // ---- stage: input projection of channels 32 ch .. +31 (hits on rows),
                 // gate, both scans, [f; b] to LDS
+                // candidate and gate pre-activation (zero accumulators cost no moves)
+                f32x16 ax[HT], gx[HT];
+                float bxv = 0.f, bgv = 0.f;
+#pragma unroll
+                for (int nt = 0; nt < HT; ++nt)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        ax[nt][q] = 0.f;
+                        gx[nt][q] = 0.f;
+                    }
+                // matrix-core phases run at raised wave priority, so that a wave
+                // entering one gets the SIMD's issue slots ahead of the vector work
+                // of the other waves
                 if (work) {
-                    const char *sl = slot();
-                    const FT *wf = reinterpret_cast<const FT *>(sl);
-                    const float *bias = reinterpret_cast<const float *>(sl + C::G1_FR * C::FRAG);
-                    // candidate and gate pre-activation (zero accumulators cost no moves)
-                    const float bxv = bias[cc];
-                    const float bgv = bias[32 + cc];  // -log2(e) b in the 16-bit modes
-                    f32x16 ax[HT], gx[HT];
-#pragma unroll
-                    for (int nt = 0; nt < HT; ++nt)
-#pragma unroll
-                        for (int q = 0; q < 16; ++q) {
-                            ax[nt][q] = 0.f;
-                            gx[nt][q] = 0.f;
-                        }
-                    // matrix-core phases run at raised wave priority, so that a wave
-                    // entering one gets the SIMD's issue slots ahead of the vector work
-                    // of the other waves
-                    __builtin_amdgcn_s_setprio(1);
                     // gate first, so that its exponentials can overlap the candidate's products
+                    const FT *wf = reinterpret_cast<const FT *>(slot());
+                    const float *bias = reinterpret_cast<const float *>(slot() + C::G1_FR * C::FRAG);
+                    bgv = bias[C::HALF ? 32 + cc : cc];  // -log2(e) b in the 16-bit modes
+                    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
                     for (int ks = 0; ks < KS1; ++ks) {
-                        const FT bg = wf[(KS1 + ks) * 64 + lane];
+                        const FT bg = wf[((C::HALF ? KS1 : 0) + ks) * 64 + lane];
 #pragma unroll
                         for (int nt = 0; nt < HT; ++nt) gx[nt] = F::mma(yf[nt][ks], bg, gx[nt]);
                     }
+                    __builtin_amdgcn_s_setprio(0);
+                }
+                if constexpr (C::NIN == 2) advance(false);  // the candidate's stage
+                if (work) {
+                    const FT *wf = reinterpret_cast<const FT *>(slot());
+                    const float *bias = reinterpret_cast<const float *>(slot() + C::G1_FR * C::FRAG);
+                    bxv = bias[cc];
+                    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
                     for (int ks = 0; ks < KS1; ++ks) {
                         const FT bx = wf[ks * 64 + lane];
@@ -835,67 +854,73 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                 }
                 if constexpr (!C::MERGE) advance(false);
 
-                // ---- stage: output projection of this chunk, K split over chunks.  The
+                // ---- stages: output projection of this chunk, K split over chunks.  The
                 // 16-bit modes accumulate straight into the residual registers; the
                 // fp32 model sums the chunk in fresh accumulators and adds it once.
-                if (work && !LAST) {
-                    const char *sl = slot() + C::G2_OFF;
-                    if constexpr (C::MERGE) wave_lds_sync();  // this wave's [f; b] stores are visible
-                    __builtin_amdgcn_s_setprio(1);
-                    const FT *wo = reinterpret_cast<const FT *>(sl);
-                    f32x16 part[C::HALF ? 1 : MT][HT];
-                    if constexpr (!C::HALF) {
 #pragma unroll
-                        for (int m = 0; m < MT; ++m)
+                for (int jo = 0; jo < C::NOUT; ++jo) {
+                    if (work && !LAST) {
+                        const char *sl = slot() + C::G2_OFF;
+                        if (jo == 0) wave_lds_sync();  // this wave's [f; b] stores are visible
+                        __builtin_amdgcn_s_setprio(1);
+                        const FT *wo = reinterpret_cast<const FT *>(sl);
+                        f32x16 part[C::HALF ? 1 : C::MPO][HT];
+                        if constexpr (!C::HALF) {
 #pragma unroll
-                            for (int nt = 0; nt < HT; ++nt)
+                            for (int m = 0; m < C::MPO; ++m)
 #pragma unroll
-                                for (int q = 0; q < 16; ++q) part[m][nt][q] = 0.f;
-                    }
+                                for (int nt = 0; nt < HT; ++nt)
 #pragma unroll
-                    for (int kk = 0; kk < KS2; ++kk) {
-                        FT bfr[HT];
-#pragma unroll
-                        for (int nt = 0; nt < HT; ++nt) {
-                            if constexpr (C::HALF) {
-                                bfr[nt] = fb_tr_frag<C, FT>(ws, nt, kk, hh, cc);
-                            } else {
-                                const float *fb = reinterpret_cast<const float *>(ws);
-                                bfr[nt] = fb[(32 * nt + cc) * C::FBS + kk * K + hh * KL];
-                            }
+                                    for (int q = 0; q < 16; ++q) part[m][nt][q] = 0.f;
                         }
 #pragma unroll
-                        for (int m = 0; m < MT; ++m) {
-                            const FT a = wo[(m * KS2 + kk) * 64 + lane];
+                        for (int kk = 0; kk < KS2; ++kk) {
+                            FT bfr[HT];
 #pragma unroll
                             for (int nt = 0; nt < HT; ++nt) {
-                                if constexpr (C::HALF)
-                                    r[m][nt] = F::mma(a, bfr[nt], r[m][nt]);
-                                else
-                                    part[m][nt] = F::mma(a, bfr[nt], part[m][nt]);
+                                if constexpr (C::HALF) {
+                                    bfr[nt] = fb_tr_frag<C, FT>(ws, nt, kk, hh, cc);
+                                } else {
+                                    const f32x4 *fb = reinterpret_cast<const f32x4 *>(
+                                        reinterpret_cast<const float *>(ws) + (32 * nt + cc) * C::FBS + kk * K + hh * KL);
+                                    const f32x4 v0 = fb[0], v1 = fb[1];
+                                    const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                                    bfr[nt] = F::pack(v);
+                                }
+                            }
+#pragma unroll
+                            for (int m = 0; m < C::MPO; ++m) {
+                                const FT a = wo[(m * KS2 + kk) * 64 + lane];
+#pragma unroll
+                                for (int nt = 0; nt < HT; ++nt) {
+                                    if constexpr (C::HALF)
+                                        r[m][nt] = F::mma(a, bfr[nt], r[m][nt]);
+                                    else
+                                        part[m][nt] = F::mma(a, bfr[nt], part[m][nt]);
+                                }
                             }
                         }
+                        if constexpr (!C::HALF) {
+#pragma unroll
+                            for (int m = 0; m < C::MPO; ++m)
+#pragma unroll
+                                for (int nt = 0; nt < HT; ++nt) r[jo * C::MPO + m][nt] += part[m][nt];
+                        }
+                        if (ch == NCH - 1) {
+                            const float *bo = reinterpret_cast<const float *>(sl + C::G2_FR * C::FRAG);
+#pragma unroll
+                            for (int m = jo * C::MPO; m < (jo + 1) * C::MPO; ++m)
+#pragma unroll
+                                for (int q = 0; q < 16; ++q) {
+                                    const float bv = bo[32 * m + 8 * (q >> 2) + 4 * hh + (q & 3)];
+#pragma unroll
+                                    for (int nt = 0; nt < HT; ++nt) r[m][nt][q] += bv;
+                                }
+                        }
+                        __builtin_amdgcn_s_setprio(0);
                     }
-                    if constexpr (!C::HALF) {
-#pragma unroll
-                        for (int m = 0; m < MT; ++m)
-#pragma unroll
-                            for (int nt = 0; nt < HT; ++nt) r[m][nt] += part[m][nt];
-                    }
-                    if (ch == NCH - 1) {
-                        const float *bo = reinterpret_cast<const float *>(sl + C::G2_FR * C::FRAG);
-#pragma unroll
-                        for (int m = 0; m < MT; ++m)
-#pragma unroll
-                            for (int q = 0; q < 16; ++q) {
-                                const float bv = bo[32 * m + 8 * (q >> 2) + 4 * hh + (q & 3)];
-#pragma unroll
-                                for (int nt = 0; nt < HT; ++nt) r[m][nt][q] += bv;
-                            }
-                    }
+                    advance(false);
                 }
-                __builtin_amdgcn_s_setprio(0);
-                advance(false);
             }
         };
 
@@ -909,20 +934,17 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
         // per chunk); unmerged, the stages are IN(0), IN(1), OUT(0), IN(2), OUT(1),
         // ..., OUT(NCH - 1).
         // out_proj: r += W_out [f; b] of the chunk in the wave's buffer (fragments
-        // at g2), plus b_out when the chunk is the layer's last.  The fp32 model sums
-        // a chunk in fresh accumulators and adds it once (to keep within 1e-5).
+        // at g2), plus b_out when the chunk is the layer's last.
         // (the lane argument: out_proj and out_bias, which run once per layer,
         // re-derive it (see KCfg::TIGHT))
         auto out_frag = [&](const char *g2, int m, int kk, int ln) -> FT {
             return reinterpret_cast<const FT *>(g2)[(m * KS2 + kk) * 64 + ln];
         };
         auto fb_frag = [&](int nt, int kk, int ln) -> FT {
-            if constexpr (C::HALF) {
+            if constexpr (C::HALF)
                 return fb_tr_frag<C, FT>(ws, nt, kk, ln >> 5, ln & 31);
-            } else {
-                const float *fb = reinterpret_cast<const float *>(ws);
-                return fb[(32 * nt + (ln & 31)) * C::FBS + kk * K + (ln >> 5) * KL];
-            }
+            else
+                return FT{};  // (the fp32 kernels have no pipelined layers)
         };
         auto out_bias = [&](const char *g2) {
             const float *bo = reinterpret_cast<const float *>(g2 + C::G2_FR * C::FRAG);
@@ -937,15 +959,6 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                 }
         };
         auto out_proj = [&](const char *g2) {
-            f32x16 part[C::HALF ? 1 : MT][HT];
-            if constexpr (!C::HALF) {
-#pragma unroll
-                for (int m = 0; m < MT; ++m)
-#pragma unroll
-                    for (int nt = 0; nt < HT; ++nt)
-#pragma unroll
-                        for (int q = 0; q < 16; ++q) part[m][nt][q] = 0.f;
-            }
             const int ln = C::TIGHT ? fresh_lane() : lane;
 #pragma unroll
             for (int kk = 0; kk < KS2; ++kk) {
@@ -956,19 +969,8 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                 for (int m = 0; m < MT; ++m) {
                     const FT a = out_frag(g2, m, kk, ln);
 #pragma unroll
-                    for (int nt = 0; nt < HT; ++nt) {
-                        if constexpr (C::HALF)
-                            r[m][nt] = F::mma(a, bfr[nt], r[m][nt]);
-                        else
-                            part[m][nt] = F::mma(a, bfr[nt], part[m][nt]);
-                    }
+                    for (int nt = 0; nt < HT; ++nt) r[m][nt] = F::mma(a, bfr[nt], r[m][nt]);
                 }
-            }
-            if constexpr (!C::HALF) {
-#pragma unroll
-                for (int m = 0; m < MT; ++m)
-#pragma unroll
-                    for (int nt = 0; nt < HT; ++nt) r[m][nt] += part[m][nt];
             }
         };
         auto layer_p = [&](auto last_c, bool prev_out) {
@@ -1002,11 +1004,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
 #pragma unroll
                         for (int q = 0; q < 16; ++q) ss = fmaf(r[m][nt][q], r[m][nt][q], ss);
                     ss += __shfl_xor(ss, 32);
-                    float rs;
-                    if constexpr (C::HALF)
-                        rs = rsqrtf(ss * (1.0f / D) + kRmsEps);
-                    else
-                        rs = 1.0f / sqrtf(ss * (1.0f / D) + kRmsEps);
+                    const float rs = rsqrtf(ss * (1.0f / D) + kRmsEps);
 #pragma unroll
                     for (int ks = 0; ks < KS1; ++ks) {
                         float v[8];
@@ -1065,19 +1063,10 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                 if (work) {
                     auto gate = [&](int e) {
                         const float g = gx[e / 16][e % 16];
-                        float a, cf;
-                        if constexpr (C::HALF) {
-                            // hardware exp2 and reciprocal; exp2 of a large argument is inf
-                            // (a = 0, cf = 1) or 0 (a = 1, cf = 0)
-                            const float ex = __builtin_amdgcn_exp2f(fmaf(g, -kLog2e, bgv));
-                            a = __builtin_amdgcn_rcpf(1.0f + ex);
-                            cf = 1.0f - a;
-                        } else {
-                            // library exp and correctly rounded division for the fp32 model
-                            const float ex = expf(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
-                            a = 1.0f / (1.0f + ex);
-                            cf = ex * a;
-                        }
+                        // hardware exp2 and reciprocal; exp2 of a large argument is inf
+                        // (a = 0, cf = 1) or 0 (a = 1, cf = 0)
+                        const float ex = __builtin_amdgcn_exp2f(fmaf(g, -kLog2e, bgv));
+                        const float a = __builtin_amdgcn_rcpf(1.0f + ex), cf = 1.0f - a;
                         AX[e] = a * (ax[e / 16][e % 16] + bxv);
                         CF[e] = cf;
                     };
@@ -1090,15 +1079,6 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         // so a run of products would hold its vector work back).
                         constexpr int NMF = MT * KS2 * HT;
                         const char *g2 = slot() + C::G2_OFF;  // the output projection's fragments
-                        f32x16 part[C::HALF ? 1 : MT][HT];
-                        if constexpr (!C::HALF) {
-#pragma unroll
-                            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                                for (int nt = 0; nt < HT; ++nt)
-#pragma unroll
-                                    for (int q = 0; q < 16; ++q) part[m][nt][q] = 0.f;
-                        }
                         FT bcur[HT], bnxt[HT], acur, anxt;
                         if constexpr (C::MERGE) wave_lds_sync();  // this wave's [f; b] stores are visible
 #pragma unroll
@@ -1117,22 +1097,13 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                             }
 #pragma unroll
                             for (int e = i * NE / NMF; e < (i + 1) * NE / NMF; ++e) gate(e);
-                            if constexpr (C::HALF)
-                                r[m][nt] = F::mma(acur, bcur[nt], r[m][nt]);
-                            else
-                                part[m][nt] = F::mma(acur, bcur[nt], part[m][nt]);
+                            r[m][nt] = F::mma(acur, bcur[nt], r[m][nt]);
                             __builtin_amdgcn_sched_barrier(0);
                             acur = anxt;
                             if (i + 1 < NMF && (i + 1) / (MT * HT) != kk) {
 #pragma unroll
                                 for (int t = 0; t < HT; ++t) bcur[t] = bnxt[t];
                             }
-                        }
-                        if constexpr (!C::HALF) {
-#pragma unroll
-                            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                                for (int nt = 0; nt < HT; ++nt) r[m][nt] += part[m][nt];
                         }
                     } else {
 #pragma unroll
@@ -1167,12 +1138,8 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         for (int i = 0; i < NP; ++i) {
                             u = fmaf(zero_lanes(CF[i], half_mask(mu0, mu1, i)), u, AX[i]);
                             U[i] = u;
-                            if constexpr (C::HALF) {
-                                if ((i & 3) == 3)
-                                    store_fb_quad<C, FE>(ws, i - 3, U[i - 3], U[i - 2], U[i - 1], U[i], 32 * hh + cc, hh);
-                            } else if (i & 1) {
-                                store_fb_pair<C>(ws, i - 1, U[i - 1], U[i], 32 * hh, hh, cc);
-                            }
+                            if ((i & 3) == 3)
+                                store_fb_quad<C, FE>(ws, i - 3, U[i - 3], U[i - 2], U[i - 1], U[i], 32 * hh + cc, hh);
                         }
                         const auto xs = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u),
                                                                          false, false);
@@ -1187,13 +1154,9 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         for (int i = NP - 1; i >= 0; --i) {
                             dn = fmaf(zero_lanes(CF[i], half_mask(md0, md1, i)), dn, AX[i]);
                             Dn[i] = dn;
-                            if constexpr (C::HALF) {
-                                if ((i & 3) == 0)
-                                    store_fb_quad<C, FE>(ws, i, Dn[i], Dn[i + 1], Dn[i + 2], Dn[i + 3], 32 - 32 * hh + cc,
-                                                         hh);
-                            } else if (!(i & 1)) {
-                                store_fb_pair<C>(ws, i, Dn[i], Dn[i + 1], 32 - 32 * hh, hh, cc);
-                            }
+                            if ((i & 3) == 0)
+                                store_fb_quad<C, FE>(ws, i, Dn[i], Dn[i + 1], Dn[i + 2], Dn[i + 3], 32 - 32 * hh + cc,
+                                                     hh);
                         }
                         if constexpr (C::PAIR) {
                             if (pb) pair_give(xba, fba, dn);
@@ -1536,14 +1499,26 @@ uint16_t to_bf16(double v) {
     return uint16_t(u >> 16);
 }
 
-// Writer of one weight stage: operand elements in the kernel's operand type,
-// biases in fp32.
+// Writer of one weight stage: operand elements in the kernel's operand type (eight
+// per lane, fp32 as its three bf16 parts), biases in fp32.
 struct StageWriter {
     int op;
     unsigned char *p;
     size_t o = 0;
+    float pend[8];  // fp32: the lane's values, written as three bf16 parts
+    int npend = 0;
     void elem(double v) {
-        if (op == OP_BF16) {
+        if (op == OP_F32) {
+            pend[npend++] = (float)v;
+            if (npend < 8) return;
+            npend = 0;
+            for (int part = 0; part < 3; ++part)
+                for (int i = 0; i < 8; ++i) {
+                    const uint16_t b = bf16_part(pend[i], part);
+                    std::memcpy(p + o, &b, 2);
+                    o += 2;
+                }
+        } else if (op == OP_BF16) {
             uint16_t b = to_bf16(v);
             std::memcpy(p + o, &b, 2);
             o += 2;
@@ -1551,8 +1526,6 @@ struct StageWriter {
             _Float16 h = (_Float16)(float)v;
             std::memcpy(p + o, &h, 2);
             o += 2;
-        } else {
-            f32(v);
         }
     }
     void f32(double v) {
@@ -1564,12 +1537,12 @@ struct StageWriter {
 
 // Stage geometry of one instance, for the host.
 struct Geom {
-    int stage, ksps, nh1, merge, g2_off, head16, pipe;
+    int stage, ksps, nh1, merge, g2_off, head16, pipe, nin, nout;
 };
 template <int D, int OP, int HT, bool PAIR = false>
 Geom geom() {
     using C = KCfg<D, OP, HT, PAIR>;
-    return {C::STAGE, C::KSPS, C::NH1, C::MERGE ? 1 : 0, C::G2_OFF, C::HEAD16 ? 1 : 0, C::PIPE ? 1 : 0};
+    return {C::STAGE, C::KSPS, C::NH1, C::MERGE ? 1 : 0, C::G2_OFF, C::HEAD16 ? 1 : 0, C::PIPE ? 1 : 0, C::NIN, C::NOUT};
 }
 // 64-hit tracks: the 16-bit modes run the pooled head on paired tiles, and the
 // end-states and front-end passes (which have no head) on 64-row wave tiles
@@ -1651,7 +1624,7 @@ extern "C" tf_status tf_weights_create(const tf_config *cfg, const float *blob, 
     if (limit > supported) return TF_EUNSUPPORTED;
     const int ht = limit <= 32 ? 1 : 2;
     const Geom G = op == OP_BF16 ? geom_d<OP_BF16>(D, ht) : op == OP_F16 ? geom_d<OP_F16>(D, ht) : geom_d<OP_F32>(D, ht);
-    const int K = half ? 16 : 2, KL = K / 2, KS1 = D / K, KS2 = 64 / K, RPK = 16 / KL;
+    const int K = 16, KL = K / 2, KS1 = D / K, KS2 = 64 / K, RPK = 16 / KL;
     const int MT = D / 32, NCH = D / 32;
     const double gs = half ? -1.4426950408889634 : 1.0;  // 16-bit modes evaluate exp2
 
@@ -1672,7 +1645,7 @@ extern "C" tf_status tf_weights_create(const tf_config *cfg, const float *blob, 
     const float *b1 = W1 + dd * dd, *W2 = b1 + dd, *b2 = W2 + 5 * dd;
 
     // the Fourier front end's projection: KF k-steps of MT fragments, KPF per stage
-    const int frag_bytes = 64 * KL * (half ? 2 : 4);
+    const int frag_bytes = 64 * KL * (half ? 2 : 6);
     const int KF = NFEAT ? (int)(KF32 / K) : 0;
     const int KPF = NFEAT ? std::min(KF, G.stage / (MT * frag_bytes)) : 1;
     const int NFS = NFEAT ? (KF + KPF - 1) / KPF : 0;
@@ -1685,7 +1658,7 @@ extern "C" tf_status tf_weights_create(const tf_config *cfg, const float *blob, 
     // projection; unmerged, per layer IN(0), IN(1), OUT(0), IN(2), OUT(1), ...,
     // OUT(NCH - 1), the last taken at the start of the next layer.
     const int n_layer_stages =
-        G.pipe ? (G.merge ? (L > 0 ? L * NCH + 1 : 0) : 2 * L * NCH) : (G.merge ? L * NCH : 2 * L * NCH);
+        G.pipe ? (G.merge ? (L > 0 ? L * NCH + 1 : 0) : 2 * L * NCH) : (G.merge ? L * NCH : (G.nin + G.nout) * L * NCH);
     auto pipe_in = [&](int l, int c) {
         return G.merge ? NFS + NCH * l + c : NFS + 2 * NCH * l + (c == 0 ? 0 : 2 * c - 1);
     };
@@ -1742,9 +1715,13 @@ extern "C" tf_status tf_weights_create(const tf_config *cfg, const float *blob, 
             // input projection B fragments: lane (g, c) value u of k-step ks holds
             // W[out 32 ch + c][in 32 m + 8 i + 4 g + j] * gain[in], with
             // (m, 4 i + j) = (ks / RPK, (ks % RPK) * KL + u); then bx[32], bg[32]
-            const int s_in = G.pipe ? pipe_in(l, ch) : s++;
+            // (fp32: the gate's fragments and bg in a stage, then the candidate's and bx in
+            // the next)
+            const int s_in = G.pipe ? pipe_in(l, ch) : s;
+            if (!G.pipe) s += G.nin;
             StageWriter w{op, hb.data() + st_off + (size_t)s_in * G.stage};
-            for (int part = 0; part < 2; ++part)
+            for (int pt = 0; pt < 2; ++pt) {
+                const int part = G.nin == 2 ? 1 - pt : pt;  // 0: candidate, 1: gate
                 for (int ks = 0; ks < KS1; ++ks)
                     for (int lane = 0; lane < 64; ++lane)
                         for (int u = 0; u < KL; ++u) {
@@ -1754,24 +1731,35 @@ extern "C" tf_status tf_weights_create(const tf_config *cfg, const float *blob, 
                             const int row = part * D + 32 * ch + c;
                             w.elem((double)Wi[(size_t)row * D + in] * g[in]);
                         }
-            for (int c = 0; c < 32; ++c) w.f32(bi[32 * ch + c]);
-            for (int c = 0; c < 32; ++c) w.f32(gs * bi[D + 32 * ch + c]);
+                if (G.nin == 2) {
+                    for (int c = 0; c < 32; ++c) w.f32(bi[part * D + 32 * ch + c]);
+                    w = StageWriter{op, hb.data() + st_off + (size_t)(s_in + 1) * G.stage};
+                }
+            }
+            if (G.nin == 1) {
+                for (int c = 0; c < 32; ++c) w.f32(bi[32 * ch + c]);
+                for (int c = 0; c < 32; ++c) w.f32(gs * bi[D + 32 * ch + c]);
+            }
             // output projection A fragments: lane (g, c) value u of k-step kk of
             // block m holds W[out 32 m + c][column of [f; b] channel
             // q = kk K + g KL + u of the chunk]; then bout[D]
-            // (merged: at g2_off in the stage of the input projection)
-            const int s_out = G.pipe ? pipe_out(l, ch) : G.merge ? s_in : s++;
-            StageWriter w2{op, hb.data() + st_off + (size_t)s_out * G.stage + G.g2_off};
-            for (int m = 0; m < MT; ++m)
-                for (int kk = 0; kk < KS2; ++kk)
-                    for (int lane = 0; lane < 64; ++lane)
-                        for (int u = 0; u < KL; ++u) {
-                            const int gg = lane / 32, c = lane % 32;
-                            const int q = kk * K + gg * KL + u;
-                            const int col = q < 32 ? 32 * ch + q : D + 32 * ch + (q - 32);
-                            w2.elem(Wo[(size_t)(32 * m + c) * 2 * D + col]);
-                        }
-            for (int c = 0; c < D; ++c) w2.f32(bo[c]);
+            // (merged: at g2_off in the stage of the input projection; fp32: half of the
+            // blocks per stage)
+            int s_out = G.pipe ? pipe_out(l, ch) : G.merge ? s_in : s;
+            if (!G.pipe && !G.merge) s += G.nout;
+            for (int jo = 0; jo < G.nout; ++jo, ++s_out) {
+                StageWriter w2{op, hb.data() + st_off + (size_t)s_out * G.stage + G.g2_off};
+                for (int m = jo * MT / G.nout; m < (jo + 1) * MT / G.nout; ++m)
+                    for (int kk = 0; kk < KS2; ++kk)
+                        for (int lane = 0; lane < 64; ++lane)
+                            for (int u = 0; u < KL; ++u) {
+                                const int gg = lane / 32, c = lane % 32;
+                                const int q = kk * K + gg * KL + u;
+                                const int col = q < 32 ? 32 * ch + q : D + 32 * ch + (q - 32);
+                                w2.elem(Wo[(size_t)(32 * m + c) * 2 * D + col]);
+                            }
+                for (int c = 0; c < D; ++c) w2.f32(bo[c]);
+            }
         }
     }
     if (G.pipe) s = NFS + n_layer_stages;
