@@ -119,6 +119,43 @@ __device__ __forceinline__ void scan_dir(float (&ax)[kMgSP], float (&cf)[kMgSP],
     }
 }
 
+// A block's states (lane (s, c), register q: channel c of tile row 16 s + q) into the
+// A operand of the next layer: lane (s, c) then holds channels 16 p + 8 s .. + 7 of
+// tile row slot_to_hit(c).  The tile is channel-major, 32 operand rows per
+// channel, channel k 4 (k / 4) elements late (so that the channels of one
+// access differ in their banks): the four states of positions 4 i .. 4 i + 3 are
+// operand rows 8 i + 4 s .. + 3 and leave in one 8-byte store, and the transposing LDS
+// read hands a lane 4 channels of one operand row from four lanes' 8-byte runs.
+// 4 stores and 4 reads a block instead of 16 two-byte stores and 2 reads.
+template <class FE>
+__device__ __forceinline__ void store_states_tr(char *tile, const float (&h)[kMgSP], int s, int c) {
+    typedef FE e4 __attribute__((ext_vector_type(4)));
+    FE *row = reinterpret_cast<FE *>(tile) + 32 * c + 4 * (c >> 2) + 4 * s;
+#pragma unroll
+    for (int i = 0; i < kMgSP / 4; ++i) {
+        // the asm keeps a state's last update (rounded to fp32) and its conversion to the
+        // operand type apart: fused into one mixed-precision fma at some positions,
+        // they would round once instead of twice, and a track's outputs would depend
+        // on where in the tile it lies
+        f32x4 v = {h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]};
+        asm volatile("" : "+v"(v));
+        *reinterpret_cast<e4 *>(row + 8 * i) = __builtin_convertvector(v, e4);
+    }
+}
+template <class FT>
+__device__ __forceinline__ FT load_states_tr(const char *tile, int p, int s, int c) {
+    typedef short s4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s4 lds_s4;
+    // (this lane fetches the run of operand rows 16 (c / 16) + 4 (c % 4) .. + 3 of
+    // channels 16 p + 8 s + (c / 4) % 4 and that + 4)
+    const int k = 8 * s + ((c >> 2) & 3);
+    const short *b = reinterpret_cast<const short *>(tile) + 32 * k + 8 * s + 16 * (c >> 4) + 4 * (c & 3) + p * (16 * 32 + 16);
+    const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)b);
+    const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(b + 4 * 32 + 4));
+    return __builtin_bit_cast(FT, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+static_assert(2 * (31 * 32 + 4 * 7 + 32) <= kMgCap * (32 * 2 + 16), "transposed states in the tile");
+
 // A wave's share of a workgroup's work: its pool (a contiguous range of tracks
 // balanced by hit rows, shared by kMgTPP waves), its place among the pool's
 // waves, the pool's window and the workgroup's tile flag.
@@ -714,19 +751,11 @@ void tf_backbone_kernel(const float *__restrict__ feats, int nf, long long n_hit
                     scan_dir<true>(AX, CF, sb0, sb1, hh);
                 else
                     scan_dir<false>(AX, CF, eb0, eb1, hh);
-                FE *tb = reinterpret_cast<FE *>(tile);
                 wave_lds_sync();  // earlier reads of the tile are done
-#pragma unroll
-                for (int i = 0; i < SP; ++i) {
-                    // (the update and its conversion kept apart, as in the layer kernel)
-                    float v = AX[i];
-                    asm volatile("" : "+v"(v));
-                    tb[(SP * hh + i) * ROWE + cc] = (FE)v;
-                }
+                store_states_tr<FE>(tile, AX, hh, cc);
                 wave_lds_sync();
-                const FE *row = tb + slot_to_hit<SP>(cc) * ROWE + 8 * hh;
-                xa2[12 * dir + 2 * ch] = *reinterpret_cast<const FT *>(row);
-                xa2[12 * dir + 2 * ch + 1] = *reinterpret_cast<const FT *>(row + 16);
+                xa2[12 * dir + 2 * ch] = load_states_tr<FT>(tile, 0, hh, cc);
+                xa2[12 * dir + 2 * ch + 1] = load_states_tr<FT>(tile, 1, hh, cc);
             }
             if (dir == 1) advance(false);
             __builtin_amdgcn_sched_barrier(0);  // blocks one after the other (registers)
@@ -736,6 +765,8 @@ void tf_backbone_kernel(const float *__restrict__ feats, int nf, long long n_hit
         // tile, stored after the block's barrier (as in the layer kernel)
         constexpr int PPR = 8;  // 16-byte pieces per row of 32 fp32 states
         constexpr int NPEND = kMgMaxTr * PPR / 64;
+        constexpr int ROWF = 32 + 4;  // row stride of the end states' rows (floats)
+        static_assert((kMgCap * ROWF + 32) * 4 <= KIN1 * C::FRAG, "state rows in the operand area");
         u32x4 pv[NPEND];
         int prow[NPEND];
         int pcol = 0;
@@ -788,26 +819,21 @@ void tf_backbone_kernel(const float *__restrict__ feats, int nf, long long n_hit
                     else
                         scan_dir<false>(AX, CF, eb0, eb1, hh);
                     pcol = dir * H + 32 * ch;
-                    // forward state at a track's last row, reverse state at its first row,
-                    // to row j of the tile (the track's index in it)
-                    constexpr int ROWF = 32 + 4;
-                    float *tf = reinterpret_cast<float *>(tile);
-                    const unsigned sw = hh ? st1 : st0;
-                    const unsigned mw = dir == 0 ? (hh ? eb1 : eb0) : sw;
-                    const int jb = hh ? __builtin_popcount(st0) - 1 : -1;
-                    wave_lds_sync();  // earlier reads of the tile are done
+                    // every row's state to the operand area (free in this layer), row r at
+                    // 36 r + 32 (r / 16) floats, then for track j of the tile the forward
+                    // state at its last row or the reverse state at its first
+                    float *tf = reinterpret_cast<float *>(xa1);
+                    wave_lds_sync();  // earlier reads of the area are done
 #pragma unroll
-                    for (int i = 0; i < SP; ++i)
-                        if ((mw >> i) & 1u) {
-                            const int j = jb + __builtin_popcount(sw & ((2u << i) - 1u));
-                            tf[j * ROWF + cc] = AX[i];
-                        }
+                    for (int i = 0; i < SP; ++i) tf[(SP * ROWF + 32) * hh + ROWF * i + cc] = AX[i];
                     wave_lds_sync();
 #pragma unroll
                     for (int p = 0; p < NPEND; ++p) {
                         const int it = lane + 64 * p, j = it / PPR, g = it % PPR;
                         prow[p] = j < k ? t_id[j] : -1;
-                        pv[p] = *reinterpret_cast<const u32x4 *>(tf + j * ROWF + 4 * g);
+                        // (entries past the tile's tracks are stale: any row of the area)
+                        const int row = (dir == 0 ? t_start[j] + t_len[j] - 1 : t_start[j]) & (kMgCap - 1);
+                        pv[p] = *reinterpret_cast<const u32x4 *>(tf + ROWF * row + 2 * (row & SP) + 4 * g);
                     }
                 }
                 advance(ch == NCHK - 1 && dir == 1);
