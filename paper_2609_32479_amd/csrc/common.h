@@ -132,6 +132,27 @@ inline uint16_t bf16_part(float v, int part) {
     return uint16_t(u >> 16);
 }
 
+// e = exp(x) for |x| <= 80 in fp32: the hardware's exp2 (1 ulp) of the rounded product
+// x log2(e), times 1 + ln(2) (its rounding error); and 1 / d for 1 <= d <= 2^126: the
+// hardware's reciprocal (1 ulp) with one Newton step.  6 and 3 instructions; the
+// library's forms cover ranges that a clamped argument cannot reach and take
+// about 14 and 11.
+__device__ __forceinline__ float exp_clamped(float x) {
+    constexpr float kLog2eLo = float(1.4426950408889634 - double(kLog2e)), kLn2 = 0.6931471805599453f;
+    const float p = x * kLog2e;
+    const float l = fmaf(x, kLog2eLo, fmaf(x, kLog2e, -p));
+    const float e = __builtin_amdgcn_exp2f(p);
+    return fmaf(e * kLn2, l, e);
+}
+__device__ __forceinline__ float rcp_clamped(float d) {
+    const float r = __builtin_amdgcn_rcpf(d);
+    return fmaf(fmaf(-d, r, 1.0f), r, r);
+}
+// v sigmoid(v), the exponent clamped (the change is below exp(-80)).
+__device__ __forceinline__ float silu_f32(float v) {
+    return v * rcp_clamped(1.0f + exp_clamped(-__builtin_amdgcn_fmed3f(v, -80.0f, 80.0f)));
+}
+
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();

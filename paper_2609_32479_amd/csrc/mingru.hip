@@ -413,8 +413,8 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                             a = __builtin_amdgcn_rcpf(1.0f + e);
                             cf = 1.0f - a;
                         } else {
-                            const float e = expf(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
-                            a = 1.0f / (1.0f + e);
+                            const float e = exp_clamped(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
+                            a = rcp_clamped(1.0f + e);
                             cf = e * a;
                         }
                         AX[i] = a * ax[i];

@@ -72,7 +72,7 @@ __device__ __forceinline__ void bias_silu(f32x16 (&acc)[MT], float inv, const fl
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const float v = fmaf(inv, acc[m][q], b1[32 * m + 8 * (q >> 2) + 4 * s + (q & 3)]);
-            acc[m][q] = v / (1.0f + expf(-__builtin_amdgcn_fmed3f(v, -80.0f, 80.0f)));
+            acc[m][q] = silu_f32(v);
         }
 }
 

@@ -752,9 +752,9 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                                 a = __builtin_amdgcn_rcpf(1.0f + e);
                                 cf = 1.0f - a;
                             } else {
-                                // library exp and correctly rounded division for the fp32 model
-                                const float e = expf(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
-                                a = 1.0f / (1.0f + e);
+                                // fp32 to the last bit or so (the fp32 model)
+                                const float e = exp_clamped(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
+                                a = rcp_clamped(1.0f + e);
                                 cf = e * a;
                             }
                             AX[nt * 16 + q] = a * (ax[nt][q] + bxv);
@@ -1408,7 +1408,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                                     sv = v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(
                                                                           __builtin_amdgcn_fmed3f(-v * kLog2e, -kGateClamp, kGateClamp)));
                                 else
-                                    sv = v / (1.0f + expf(-__builtin_amdgcn_fmed3f(v, -80.0f, 80.0f)));
+                                    sv = silu_f32(v);
                                 hid[mu][q] = sv;
                             }
                     }
