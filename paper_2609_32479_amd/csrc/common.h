@@ -93,6 +93,17 @@ template <> struct Frag<OP_F32> {
         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, c, 0, 0, 0);
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, c, 0, 0, 0);
     }
+    // The same in two sums, products of one taking turns with the other's: for a wave
+    // that has the SIMD to itself, whose dependent products run at 44 cycles each
+    // instead of 32.
+    static __device__ __forceinline__ void mma2(const T &a, const T &b, f32x16 &c, f32x16 &d) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, c, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, d, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, c, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, d, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, c, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, d, 0, 0, 0);
+    }
     static __device__ __forceinline__ T pack(const float *v) {
         typedef float f2 __attribute__((ext_vector_type(2)));
         typedef __bf16 b2 __attribute__((ext_vector_type(2)));
@@ -151,6 +162,32 @@ __device__ __forceinline__ float rcp_clamped(float d) {
 // v sigmoid(v), the exponent clamped (the change is below exp(-80)).
 __device__ __forceinline__ float silu_f32(float v) {
     return v * rcp_clamped(1.0f + exp_clamped(-__builtin_amdgcn_fmed3f(v, -80.0f, 80.0f)));
+}
+
+// N products in a row whose weight fragments come from LDS: step(i, fragment i) for i in
+// order, with the fragments of the next DEPTH - 1 steps always on their way (load(i)
+// reads one).  The fences keep that order: left to itself the compiler reads two
+// fragments, waits for both (an LDS read under load takes longer than two products)
+// and only then issues their products.  DEPTH 0: left to the compiler (for kernels
+// that have no registers for it).
+template <int N, int DEPTH, class Load, class Step>
+__device__ __forceinline__ void ring_products(Load load, Step step) {
+    if constexpr (DEPTH == 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) step(i, load(i));
+    } else {
+        decltype(load(0)) w[DEPTH];
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i)
+            if (i < N) w[i] = load(i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            step(i, w[i % DEPTH]);
+            if (i + DEPTH < N) w[i % DEPTH] = load(i + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
 }
 
 __device__ __forceinline__ void wave_lds_sync() {

@@ -278,12 +278,16 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
 #pragma unroll
     for (int q = 0; q < C::NSLOT - 1; ++q) copy_stage<C>(stages, q % S, slot_lds(q), wid, lane);
     // Stage q (counted across tiles) lives in slot q % NSLOT.  Every stage ends
-    // with all of this wave's memory operations complete and a barrier, after
-    // which stage q + NSLOT goes into the slot just read; the last stage of a
+    // with this wave's copies of the next stage complete (its loads complete in
+    // order, so no more than the younger stages' may be outstanding) and a barrier,
+    // after which stage q + NSLOT goes into the slot just read; the last stage of a
     // tile leaves that copy to the start of the next tile.
     int q = 0;
     auto advance = [&](bool last) {
-        wait_vmcnt<0>();
+        if (last)
+            wait_vmcnt<0>();
+        else
+            wait_vmcnt<(C::NSLOT - 2) * C::LPW>();
         lds_barrier();
         if (!last) copy_stage<C>(stages, (q + C::NSLOT) % S, slot_lds(q + C::NSLOT), wid, lane);
         ++q;
@@ -360,9 +364,12 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
 
         // acc = X W^T of the weight block that starts in the current stage at `off`
         // (its later stages taken as they come), without the bias; leaves the ring at the
-        // block's last stage.  Two accumulators where one wave has the SIMD to itself:
-        // a chain of dependent products runs at 44 cycles each instead of 32.
-        auto products = [&](f32x16 &acc, int off) {
+        // block's last stage.  beside(ks): vector work of k-step ks.  In the fp32 kernels,
+        // where a k-step is six products, the order is set by hand: the next k-step's
+        // fragments are read first (left to itself the compiler reads each right before
+        // its product, and one wave per SIMD waits out the latency twice a k-step), and
+        // the vector work is spread between the products, as a wave issues in order.
+        auto products = [&](f32x16 &acc, int off, auto beside) {
             f32x16 odd;
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[i] = odd[i] = 0.f;
@@ -370,55 +377,85 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
             for (int sp = 0; sp < C::SPB; ++sp) {
                 if (sp > 0) advance(false);
                 if (work) {
-                    const FT *wf = reinterpret_cast<const FT *>(slot() + off);
+                    const FT *wf = reinterpret_cast<const FT *>(slot() + off) + lane;
                     __builtin_amdgcn_s_setprio(1);
+                    if constexpr (C::HALF) {
+                        ring_products<C::KPS, 4>([&](int i) -> FT { return wf[i * 64]; },
+                                                 [&](int ks, const FT &w) {
+                                                     acc = F::mma(xa[ks], w, acc);
+                                                     beside(ks);
+                                                 });
+                    } else {
+                        FT wn = wf[0];
 #pragma unroll
-                    for (int kl = 0; kl < C::KPS; ++kl) {
-                        const int ks = sp * C::KPS + kl;
-                        if (C::WAVES == 4 && (kl & 1))
-                            odd = F::mma(xa[ks], wf[kl * 64 + lane], odd);
-                        else
-                            acc = F::mma(xa[ks], wf[kl * 64 + lane], acc);
+                        for (int kl = 0; kl < C::KPS; ++kl) {
+                            const int ks = sp * C::KPS + kl;
+                            const FT wc = wn;
+                            if (kl + 1 < C::KPS) wn = wf[(kl + 1) * 64];
+                            if constexpr (C::WAVES == 4)
+                                F::mma2(xa[ks], wc, acc, odd);
+                            else
+                                acc = F::mma(xa[ks], wc, acc);
+                            beside(ks);
+                            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // the next k-step's LDS reads
+#pragma unroll
+                            for (int i = 0; i < 6; ++i) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a product
+                                __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);  // vector instructions
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
                     __builtin_amdgcn_s_setprio(0);
                 }
             }
-            if constexpr (C::WAVES == 4) acc += odd;
+            if constexpr (C::WAVES == 4 && !C::HALF) acc += odd;
         };
 
         // ---- chunks of 32 hidden channels, forward then reverse direction
         for (int ch = 0; ch < NCHK; ++ch) {
 #pragma unroll
             for (int dir = 0; dir < 2; ++dir) {
-                // candidate block: rows dir 2H + 32 ch + cc of the layer's weights
+                // gate block: rows dir 2H + H + 32 ch + cc of the layer's weights; bias
+                // pre-scaled by -log2(e) in the 16-bit modes (exp2 below)
                 f32x16 ax, gx;
-                products(ax, 0);
-                if (work) ax += reinterpret_cast<const float *>(slot() + C::KPS * C::FRAG)[cc];
+                float bgv = 0.f;
+                products(gx, 0, [](int) {});
+                if (work) bgv = reinterpret_cast<const float *>(slot() + C::KPS * C::FRAG)[cc];
                 if constexpr (!C::MERGE) advance(false);
                 flush();  // the previous block's outputs
-                // the gate block: the next stage, or the second block of this one; rows
-                // dir 2H + H + 32 ch + cc; bias pre-scaled by -log2(e) in the 16-bit modes
-                // (exp2 below)
-                constexpr int GOFF = C::MERGE ? C::BLOCK : 0;
-                products(gx, GOFF);
+                // the candidate block: the next stage, or the second block of this one; rows
+                // dir 2H + 32 ch + cc.  Beside its products the gates a = sigmoid(g), which
+                // need the gate block alone: the update adds a x and keeps 1 - a of the state.
+                // (With the gates after both blocks the fp32 layer of input 384, one wave per
+                // SIMD, kept the matrix cores busy 39 % of the time.)
+                constexpr int XOFF = C::MERGE ? C::BLOCK : 0;
+                float CF[SP];
+                if constexpr (!C::HALF) {
+#pragma unroll
+                    for (int i = 0; i < SP; ++i) CF[i] = 0.f;
+                }
+                products(ax, XOFF, [&](int ks) {
+#pragma unroll
+                    for (int i = ks * SP / KIN; i < (ks + 1) * SP / KIN; ++i) {
+                        if constexpr (C::HALF) {
+                            const float e = __builtin_amdgcn_exp2f(fmaf(gx[i], -kLog2e, bgv));
+                            gx[i] = __builtin_amdgcn_rcpf(1.0f + e);
+                        } else {
+                            const float e = exp_clamped(-__builtin_amdgcn_fmed3f(gx[i] + bgv, -80.0f, 80.0f));
+                            const float a = rcp_clamped(1.0f + e);
+                            gx[i] = a;
+                            CF[i] = e * a;
+                        }
+                    }
+                });
                 if (work) {
-                    const float bgv = reinterpret_cast<const float *>(slot() + GOFF + C::KPS * C::FRAG)[cc];
-                    float AX[SP], CF[SP];
+                    const float bxv = reinterpret_cast<const float *>(slot() + XOFF + C::KPS * C::FRAG)[cc];
+                    float AX[SP];
 #pragma unroll
                     for (int i = 0; i < SP; ++i) {
-                        const float g = gx[i];
-                        float a, cf;
-                        if constexpr (C::HALF) {
-                            const float e = __builtin_amdgcn_exp2f(fmaf(g, -kLog2e, bgv));
-                            a = __builtin_amdgcn_rcpf(1.0f + e);
-                            cf = 1.0f - a;
-                        } else {
-                            const float e = exp_clamped(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
-                            a = rcp_clamped(1.0f + e);
-                            cf = e * a;
-                        }
-                        AX[i] = a * ax[i];
-                        CF[i] = cf;
+                        if constexpr (C::HALF) CF[i] = 1.0f - gx[i];
+                        AX[i] = gx[i] * (ax[i] + bxv);
                     }
                     if (dir == 0)
                         scan_dir<true>(AX, CF, sb0, sb1, hh);
@@ -428,27 +465,38 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                     char *tile = smem + C::WAVE0 + wid * C::WAVE_BYTES + C::TB_OFF;
                     wave_lds_sync();  // the previous block's reads of the tile are done
                     if constexpr (LAST) {
-                        // forward state at a track's last row, reverse state at its first row,
-                        // to row j of the tile (the track's index in it: the number of track
-                        // starts up to the row, less one)
+                        // the tracks' states, forward at a track's last row, reverse at its first
                         constexpr int ROWF = 32 + 4;  // row stride (floats)
-                        static_assert(kMgMaxTr * ROWF * 4 <= kMgCap * C::ROWB, "end-state rows in the tile");
                         float *tf = reinterpret_cast<float *>(tile);
-                        const unsigned sw = hh ? st1 : st0;
-                        const unsigned mw = dir == 0 ? (hh ? eb1 : eb0) : sw;
-                        const int jb = hh ? __builtin_popcount(st0) - 1 : -1;
+                        if constexpr (!C::HALF) {
+                            // every row to the tile, the tracks' read from it
+                            static_assert(C::HALF || kMgCap * ROWF * 4 <= kMgCap * C::ROWB, "state rows in the tile");
 #pragma unroll
-                        for (int i = 0; i < SP; ++i)
-                            if ((mw >> i) & 1u) {
-                                const int j = jb + __builtin_popcount(sw & ((2u << i) - 1u));
-                                tf[j * ROWF + cc] = AX[i];
-                            }
+                            for (int i = 0; i < SP; ++i) tf[(SP * hh + i) * ROWF + cc] = AX[i];
+                        } else {
+                            // (a 16-bit tile has no room for all rows) to row j of the tile, the
+                            // track's index in it: the track starts up to the row, less one
+                            static_assert(kMgMaxTr * ROWF * 4 <= kMgCap * C::ROWB, "end-state rows in the tile");
+                            const unsigned sw = hh ? st1 : st0;
+                            const unsigned mw = dir == 0 ? (hh ? eb1 : eb0) : sw;
+                            const int jb = hh ? __builtin_popcount(st0) - 1 : -1;
+#pragma unroll
+                            for (int i = 0; i < SP; ++i)
+                                if ((mw >> i) & 1u) {
+                                    const int j = jb + __builtin_popcount(sw & ((2u << i) - 1u));
+                                    tf[j * ROWF + cc] = AX[i];
+                                }
+                        }
                         wave_lds_sync();
 #pragma unroll
                         for (int p = 0; p < NPEND; ++p) {
                             const int it = lane + 64 * p, j = it / PPR, g = it % PPR;
                             prow[p] = j < k ? t_id[j] : -1;
-                            pv[p] = *reinterpret_cast<const u32x4 *>(tf + j * ROWF + g * VPP);
+                            // (entries past the tile's tracks are stale: any row of the tile)
+                            int row = j;
+                            if constexpr (!C::HALF)
+                                row = (dir == 0 ? t_start[j] + t_len[j] - 1 : t_start[j]) & (kMgCap - 1);
+                            pv[p] = *reinterpret_cast<const u32x4 *>(tf + row * ROWF + g * VPP);
                         }
                     } else {
                         constexpr int ROWE = C::ROWB / (int)sizeof(FE);  // tile row stride (elements)
@@ -783,37 +831,44 @@ void tf_backbone_kernel(const float *__restrict__ feats, int nf, long long n_hit
         for (int ch = 0; ch < NCHK; ++ch) {
 #pragma unroll
             for (int dir = 0; dir < 2; ++dir) {
-                f32x16 ax;
+                f32x16 gx;
+                float bgv = 0.f;
                 if (work) {
-                    const FT *wc = reinterpret_cast<const FT *>(slot());
+                    const FT *wg = reinterpret_cast<const FT *>(slot());
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) ax[i] = 0.f;
+                    for (int i = 0; i < 16; ++i) gx[i] = 0.f;
                     __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-                    for (int ks = 0; ks < KIN2; ++ks) {
-                        ax = F::mma(xa2[ks], wc[ks * 64 + lane], ax);
-                        if (ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four fragments in flight
-                    }
+                    ring_products<KIN2, 4>([&](int ks) -> FT { return wg[ks * 64 + lane]; },
+                                           [&](int ks, const FT &w) { gx = F::mma(xa2[ks], w, gx); });
                     __builtin_amdgcn_s_setprio(0);
-                    ax += reinterpret_cast<const float *>(slot() + KIN2 * C::FRAG)[cc];
+                    bgv = reinterpret_cast<const float *>(slot() + KIN2 * C::FRAG)[cc];
                 }
                 advance(false);
                 flush();  // the previous block's end states
                 if (work) {
-                    const FT *wg = reinterpret_cast<const FT *>(slot());
-                    f32x16 gx;
+                    // the candidate's products, beside them the gates (which need the gate block
+                    // alone), in place of their pre-activations
+                    const FT *wc = reinterpret_cast<const FT *>(slot());
+                    f32x16 ax;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) gx[i] = 0.f;
+                    for (int i = 0; i < 16; ++i) ax[i] = 0.f;
                     __builtin_amdgcn_s_setprio(1);
+                    ring_products<KIN2, 4>(
+                        [&](int ks) -> FT { return wc[ks * 64 + lane]; },
+                        [&](int ks, const FT &w) {
+                            ax = F::mma(xa2[ks], w, ax);
 #pragma unroll
-                    for (int ks = 0; ks < KIN2; ++ks) {
-                        gx = F::mma(xa2[ks], wg[ks * 64 + lane], gx);
-                        if (ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-                    }
+                            for (int i = ks * SP / KIN2; i < (ks + 1) * SP / KIN2; ++i)
+                                gx[i] = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fmaf(gx[i], -kLog2e, bgv)));
+                        });
                     __builtin_amdgcn_s_setprio(0);
-                    const float bgv = reinterpret_cast<const float *>(slot() + KIN2 * C::FRAG)[cc];
+                    const float bxv = reinterpret_cast<const float *>(slot() + KIN2 * C::FRAG)[cc];
                     float AX[SP], CF[SP];
-                    gate(ax, gx, bgv, AX, CF);
+#pragma unroll
+                    for (int i = 0; i < SP; ++i) {
+                        AX[i] = gx[i] * (ax[i] + bxv);
+                        CF[i] = 1.0f - gx[i];
+                    }
                     if (dir == 0)
                         scan_dir<true>(AX, CF, sb0, sb1, hh);
                     else
@@ -993,8 +1048,8 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
             return st;
         }
     }
-    // layer stages: for each 32-channel chunk and direction, the candidate block then
-    // the gate block
+    // layer stages: for each 32-channel chunk and direction, the gate block then the
+    // candidate block
     std::vector<size_t> loff(L);
     size_t total = 0;
     for (int l = 0; l < L; ++l) {
@@ -1047,23 +1102,24 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
         const int din = l == 0 ? d : 2 * H;
         const MGeom g = stage_bytes_of(op, din);
         const float *W = lw, *b = lw + (size_t)4 * H * din;
-        // layered: for each 32-channel chunk and direction the candidate block starts
-        // a stage; the gate block follows it in the same stage (merged) or starts the
-        // next one.  Fused: layer 0 merged, layer 1 one block per stage.
+        // layered: for each 32-channel chunk and direction the gate block starts a
+        // stage; the candidate block follows it in the same stage (merged) or starts
+        // the next one.  Fused: layer 0 merged (candidate first), layer 1 one block per
+        // stage, the gate's first.
         unsigned char *dst = hb.data() + loff[l];
         unsigned char *fdst = fusable ? hb.data() + bb_off + (size_t)(bb_nfs + (l == 0 ? 0 : BC::L1_STAGES)) * BC::STAGE
                                       : nullptr;
         for (int ch = 0; ch < H / 32; ++ch)
             for (int dir = 0; dir < 2; ++dir)
-                for (int part = 0; part < 2; ++part) {
+                for (int part = 1; part >= 0; --part) {  // 1: gate, 0: candidate
                     const int rbase = dir * 2 * H + part * H + 32 * ch;
                     for (int sp = 0; sp < g.spb; ++sp) {
                         put_part(dst, W, b, din, rbase, part == 1, sp * din / K / g.spb, din / K / g.spb);
-                        dst += (g.merge && part == 0) ? g.block : (g.merge ? g.stage - g.block : g.stage);
+                        dst += (g.merge && part == 1) ? g.block : (g.merge ? g.stage - g.block : g.stage);
                     }
                     if (fusable) {
                         put_block(fdst + (l == 0 ? (2 * dir + part) * BC::BLOCK1 : 0), W, b, din, rbase, part == 1);
-                        fdst += l == 0 ? (dir == 1 && part == 1 ? BC::STAGE : 0) : BC::STAGE;
+                        fdst += l == 0 ? (dir == 1 && part == 0 ? BC::STAGE : 0) : BC::STAGE;
                     }
                 }
         lw += (size_t)4 * H * din + (size_t)4 * H;

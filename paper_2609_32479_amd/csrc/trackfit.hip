@@ -344,6 +344,9 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
     constexpr int KS1 = C::KS1, KS2 = C::KS2, RPK = C::RPK, KPB = C::KPB, NCH = C::NCH;
     constexpr int MAXTR = C::MAXTR, TMAXTR = C::TMAXTR;
     constexpr int OUTW = STATES ? 2 * D : 5;  // floats per output row (head, states)
+    // weight fragments on their way (ring_products), as many as the registers allow
+    // without scratch (fp32: 65 536 tracks 2.77 ms without, 2.88 ms with two)
+    constexpr int kRing = !C::HALF ? 0 : D <= 128 ? 4 : OUTM == OUT_HEAD ? 3 : 0;
 
     __shared__ __attribute__((aligned(16))) char smem[C::LDS_BYTES];
     const int lane = threadIdx.x & 63;
@@ -711,17 +714,17 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                 // entering one gets the SIMD's issue slots ahead of the vector work
                 // of the other waves
                 if (work) {
-                    // gate first, so that its exponentials can overlap the candidate's products
+                    // gate first, so that its arithmetic can run beside the candidate's products
                     const FT *wf = reinterpret_cast<const FT *>(slot());
                     const float *bias = reinterpret_cast<const float *>(slot() + C::G1_FR * C::FRAG);
                     bgv = bias[C::HALF ? 32 + cc : cc];  // -log2(e) b in the 16-bit modes
                     __builtin_amdgcn_s_setprio(1);
+                    ring_products<KS1, kRing>([&](int i) -> FT { return wf[((C::HALF ? KS1 : 0) + i) * 64 + lane]; },
+                                              [&](int i, const FT &b) {
 #pragma unroll
-                    for (int ks = 0; ks < KS1; ++ks) {
-                        const FT bg = wf[((C::HALF ? KS1 : 0) + ks) * 64 + lane];
-#pragma unroll
-                        for (int nt = 0; nt < HT; ++nt) gx[nt] = F::mma(yf[nt][ks], bg, gx[nt]);
-                    }
+                                                  for (int nt = 0; nt < HT; ++nt)
+                                                      gx[nt] = F::mma(yf[nt][i], b, gx[nt]);
+                                              });
                     __builtin_amdgcn_s_setprio(0);
                 }
                 if constexpr (C::NIN == 2) advance(false);  // the candidate's stage
@@ -729,31 +732,48 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     const FT *wf = reinterpret_cast<const FT *>(slot());
                     const float *bias = reinterpret_cast<const float *>(slot() + C::G1_FR * C::FRAG);
                     bxv = bias[cc];
+                    // beside the candidate's products the gates a = sigmoid(g), which need the
+                    // gate's pre-activations alone, in their place: a in the 16-bit modes,
+                    // exp(-g) in the fp32 model.  (A wave issues in order, so that a run of
+                    // products would hold its vector work back.)
+                    auto gate = [&](int i) {
+                        const float g = gx[i / 16][i % 16];
+                        if constexpr (C::HALF)
+                            // hardware exp2 and reciprocal; exp2 of a large argument is inf
+                            // (a = 0, cf = 1) or 0 (a = 1, cf = 0)
+                            gx[i / 16][i % 16] = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fmaf(g, -kLog2e, bgv)));
+                        else
+                            gx[i / 16][i % 16] = exp_clamped(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
+                    };
+                    // (One tile of 32 rows and the pooled head: the others have no registers left
+                    // for it; fp32, two waves per SIMD: 65 536 tracks 2.77 ms without, 2.83 ms
+                    // with it.)
+                    constexpr bool BESIDE = C::HALF && HT == 1 && OUTM == OUT_HEAD;
+                    constexpr int NE = HT * 16;
                     __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-                    for (int ks = 0; ks < KS1; ++ks) {
-                        const FT bx = wf[ks * 64 + lane];
+                    ring_products<KS1, kRing>([&](int i) -> FT { return wf[i * 64 + lane]; },
+                                              [&](int ks, const FT &bx) {
 #pragma unroll
                         for (int nt = 0; nt < HT; ++nt) ax[nt] = F::mma(yf[nt][ks], bx, ax[nt]);
-                    }
+                        if constexpr (BESIDE) {
+#pragma unroll
+                            for (int i = ks * NE / KS1; i < (ks + 1) * NE / KS1; ++i) gate(i);
+                        }
+                    });
                     __builtin_amdgcn_s_setprio(0);
-                    // gate a = sigmoid(g): the update adds a x and keeps cf = 1 - a of the state
-                    float AX[HT * 16], CF[HT * 16];
+                    // the update adds a x and keeps cf = 1 - a of the state
+                    float AX[NE], CF[NE];
 #pragma unroll
                     for (int nt = 0; nt < HT; ++nt)
 #pragma unroll
                         for (int q = 0; q < 16; ++q) {
-                            const float g = gx[nt][q];
                             float a, cf;
+                            if constexpr (!BESIDE) gate(nt * 16 + q);
                             if constexpr (C::HALF) {
-                                // hardware exp2 and reciprocal; exp2 of a large argument is inf
-                                // (a = 0, cf = 1) or 0 (a = 1, cf = 0)
-                                const float e = __builtin_amdgcn_exp2f(fmaf(g, -kLog2e, bgv));
-                                a = __builtin_amdgcn_rcpf(1.0f + e);
+                                a = gx[nt][q];
                                 cf = 1.0f - a;
                             } else {
-                                // fp32 to the last bit or so (the fp32 model)
-                                const float e = exp_clamped(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
+                                const float e = gx[nt][q];  // fp32 to the last bit or so (the fp32 model)
                                 a = rcp_clamped(1.0f + e);
                                 cf = e * a;
                             }
@@ -873,24 +893,26 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
 #pragma unroll
                                     for (int q = 0; q < 16; ++q) part[m][nt][q] = 0.f;
                         }
+                        FT bfr[HT];
+                        ring_products<KS2 * C::MPO, kRing>(
+                            [&](int i) -> FT { return wo[((i % C::MPO) * KS2 + i / C::MPO) * 64 + lane]; },
+                            [&](int i, const FT &a) {
+                                const int kk = i / C::MPO, m = i % C::MPO;
+                                if (m == 0) {
 #pragma unroll
-                        for (int kk = 0; kk < KS2; ++kk) {
-                            FT bfr[HT];
-#pragma unroll
-                            for (int nt = 0; nt < HT; ++nt) {
-                                if constexpr (C::HALF) {
-                                    bfr[nt] = fb_tr_frag<C, FT>(ws, nt, kk, hh, cc);
-                                } else {
-                                    const f32x4 *fb = reinterpret_cast<const f32x4 *>(
-                                        reinterpret_cast<const float *>(ws) + (32 * nt + cc) * C::FBS + kk * K + hh * KL);
-                                    const f32x4 v0 = fb[0], v1 = fb[1];
-                                    const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                                    bfr[nt] = F::pack(v);
+                                    for (int nt = 0; nt < HT; ++nt) {
+                                        if constexpr (C::HALF) {
+                                            bfr[nt] = fb_tr_frag<C, FT>(ws, nt, kk, hh, cc);
+                                        } else {
+                                            const f32x4 *fb = reinterpret_cast<const f32x4 *>(
+                                                reinterpret_cast<const float *>(ws) + (32 * nt + cc) * C::FBS + kk * K +
+                                                hh * KL);
+                                            const f32x4 v0 = fb[0], v1 = fb[1];
+                                            const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                                            bfr[nt] = F::pack(v);
+                                        }
+                                    }
                                 }
-                            }
-#pragma unroll
-                            for (int m = 0; m < C::MPO; ++m) {
-                                const FT a = wo[(m * KS2 + kk) * 64 + lane];
 #pragma unroll
                                 for (int nt = 0; nt < HT; ++nt) {
                                     if constexpr (C::HALF)
@@ -898,8 +920,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                                     else
                                         part[m][nt] = F::mma(a, bfr[nt], part[m][nt]);
                                 }
-                            }
-                        }
+                            });
                         if constexpr (!C::HALF) {
 #pragma unroll
                             for (int m = 0; m < C::MPO; ++m)
@@ -960,18 +981,17 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
         };
         auto out_proj = [&](const char *g2) {
             const int ln = C::TIGHT ? fresh_lane() : lane;
+            FT bfr[HT];
+            ring_products<KS2 * MT, kRing>([&](int i) -> FT { return out_frag(g2, i % MT, i / MT, ln); },
+                                           [&](int i, const FT &a) {
+                                               if (i % MT == 0) {
 #pragma unroll
-            for (int kk = 0; kk < KS2; ++kk) {
-                FT bfr[HT];
+                                                   for (int nt = 0; nt < HT; ++nt) bfr[nt] = fb_frag(nt, i / MT, ln);
+                                               }
 #pragma unroll
-                for (int nt = 0; nt < HT; ++nt) bfr[nt] = fb_frag(nt, kk, ln);
-#pragma unroll
-                for (int m = 0; m < MT; ++m) {
-                    const FT a = out_frag(g2, m, kk, ln);
-#pragma unroll
-                    for (int nt = 0; nt < HT; ++nt) r[m][nt] = F::mma(a, bfr[nt], r[m][nt]);
-                }
-            }
+                                               for (int nt = 0; nt < HT; ++nt)
+                                                   r[i % MT][nt] = F::mma(a, bfr[nt], r[i % MT][nt]);
+                                           });
         };
         auto layer_p = [&](auto last_c, bool prev_out) {
             constexpr bool LAST = decltype(last_c)::value;
@@ -1039,18 +1059,17 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     // input projection: the gate's products first, so that the gate
                     // arithmetic can start while the candidate's are still running
                     __builtin_amdgcn_s_setprio(1);
+                    ring_products<2 * KS1, kRing>(
+                        [&](int i) -> FT { return wf[(i < KS1 ? KS1 + i : i - KS1) * 64 + lane]; },
+                        [&](int i, const FT &b) {
 #pragma unroll
-                    for (int ks = 0; ks < KS1; ++ks) {
-                        const FT bg = wf[(KS1 + ks) * 64 + lane];
-#pragma unroll
-                        for (int nt = 0; nt < HT; ++nt) gx[nt] = F::mma(yf[nt][ks], bg, gx[nt]);
-                    }
-#pragma unroll
-                    for (int ks = 0; ks < KS1; ++ks) {
-                        const FT bx = wf[ks * 64 + lane];
-#pragma unroll
-                        for (int nt = 0; nt < HT; ++nt) ax[nt] = F::mma(yf[nt][ks], bx, ax[nt]);
-                    }
+                            for (int nt = 0; nt < HT; ++nt) {
+                                if (i < KS1)
+                                    gx[nt] = F::mma(yf[nt][i], b, gx[nt]);
+                                else
+                                    ax[nt] = F::mma(yf[nt][i - KS1], b, ax[nt]);
+                            }
+                        });
                     __builtin_amdgcn_s_setprio(0);
                 }
                 if constexpr (!C::MERGE) advance(false);  // the input projection's stage is read
