@@ -1357,16 +1357,25 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         if (!hc) continue;
                         for (int tr = tr0 + hh; tr < tr1; tr += 2) {
                             const int s0 = t_start[tr], len = t_len[tr];
-                            // in order of u, eight independent reads at a time (rows past the
-                            // track's end are read in bounds and not added)
+                            // in order of u, eight independent reads at a time.  One tile per wave:
+                            // rows past the track's end are read (at most 7 past the scratch's CAP
+                            // rows, in the MAXTR pooled rows behind them) and count as 0, so that a
+                            // read is one instruction; a pair's rows lie in two scratches, and the
+                            // last is repeated.
+                            static_assert(C::MAXTR >= 7, "rows read past the scratch");
                             float sum = 0.f;
-                            for (int u0 = 0; u0 < len; u0 += 8) {
+                            const float *row = stage + s0 * C::STS + cc;
+                            for (int u0 = 0; u0 < len; u0 += 8, row += 8 * C::STS) {
                                 float v[8];
 #pragma unroll
-                                for (int i = 0; i < 8; ++i) v[i] = prow_of(s0 + (u0 + i < len ? u0 + i : len - 1))[cc];
+                                for (int i = 0; i < 8; ++i) {
+                                    if constexpr (C::PAIR)
+                                        v[i] = prow_of(s0 + (u0 + i < len ? u0 + i : len - 1))[cc];
+                                    else
+                                        v[i] = row[i * C::STS];
+                                }
 #pragma unroll
-                                for (int i = 0; i < 8; ++i)
-                                    if (u0 + i < len) sum += v[i];
+                                for (int i = 0; i < 8; ++i) sum += u0 + i < len ? v[i] : 0.f;
                             }
                             pblk[(tr - tr0) * C::STS + cc] = sum / (float)len;  // 0 / 0 = NaN for an empty track
                         }
