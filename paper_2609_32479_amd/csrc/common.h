@@ -121,8 +121,11 @@ template <> struct Frag<OP_F32> {
         return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
     }
 };
-// The same split on the host (the weights): part 0, 1 or 2 as bf16 bits.
-inline uint16_t bf16_part(float v, int part) {
+// The same split on the host (the weights): the parts' bf16 bits.
+struct Bf16Parts {
+    uint16_t part[3];
+};
+inline Bf16Parts bf16_parts(float v) {
     auto bits = [](float x) {
         uint32_t u;
         __builtin_memcpy(&u, &x, 4);
@@ -133,14 +136,11 @@ inline uint16_t bf16_part(float v, int part) {
         __builtin_memcpy(&x, &u, 4);
         return x;
     };
-    uint32_t u = bits(v) & 0xffff0000u;
-    if (part > 0) {
-        v -= value(u);
-        u = bits(v);
-        u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
-        if (part > 1) u = bits(v - value(u));
-    }
-    return uint16_t(u >> 16);
+    const uint32_t h = bits(v) & 0xffff0000u;
+    const float r = v - value(h);
+    uint32_t m = bits(r);
+    m = (m + 0x7fffu + ((m >> 16) & 1u)) & 0xffff0000u;
+    return {{uint16_t(h >> 16), uint16_t(m >> 16), uint16_t(bits(r - value(m)) >> 16)}};
 }
 
 // e = exp(x) for |x| <= 80 in fp32: the hardware's exp2 (1 ulp) of the rounded product

@@ -1072,9 +1072,12 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
     // value e of the lane whose eight values start at element i (fp32: the three
     // bf16 parts of all eight one after the other)
     auto put_elem = [&](unsigned char *sp, size_t i, int e, float v) {
-        for (int part = 0; part < (half ? 1 : 3); ++part) {
-            const uint16_t bb = half ? bits16(v, bf) : bf16_part(v, part);
-            std::memcpy(sp + 2 * (half ? i + e : 3 * i + 8 * part + e), &bb, 2);
+        if (half) {
+            const uint16_t bb = bits16(v, bf);
+            std::memcpy(sp + 2 * (i + e), &bb, 2);
+        } else {
+            const Bf16Parts b = bf16_parts(v);
+            for (int part = 0; part < 3; ++part) std::memcpy(sp + 2 * (3 * i + 8 * part + e), &b.part[part], 2);
         }
     };
     // k-steps k0 .. k0 + nk - 1 of one weight block: lane (s, c) value e of k-step ks

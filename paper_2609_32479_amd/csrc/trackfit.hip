@@ -1540,12 +1540,11 @@ struct StageWriter {
             pend[npend++] = (float)v;
             if (npend < 8) return;
             npend = 0;
-            for (int part = 0; part < 3; ++part)
-                for (int i = 0; i < 8; ++i) {
-                    const uint16_t b = bf16_part(pend[i], part);
-                    std::memcpy(p + o, &b, 2);
-                    o += 2;
-                }
+            for (int i = 0; i < 8; ++i) {
+                const Bf16Parts b = bf16_parts(pend[i]);
+                for (int part = 0; part < 3; ++part) std::memcpy(p + o + 16 * part + 2 * i, &b.part[part], 2);
+            }
+            o += 48;
         } else if (op == OP_BF16) {
             uint16_t b = to_bf16(v);
             std::memcpy(p + o, &b, 2);
