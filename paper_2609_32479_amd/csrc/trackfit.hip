@@ -1357,25 +1357,24 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         if (!hc) continue;
                         for (int tr = tr0 + hh; tr < tr1; tr += 2) {
                             const int s0 = t_start[tr], len = t_len[tr];
-                            // in order of u, eight independent reads at a time.  One tile per wave:
-                            // rows past the track's end are read (at most 7 past the scratch's CAP
-                            // rows, in the MAXTR pooled rows behind them) and count as 0, so that a
-                            // read is one instruction; a pair's rows lie in two scratches, and the
-                            // last is repeated.
+                            // in row order, eight independent reads at a time; a pair's rows lie in
+                            // the scratches of its two waves, one after the other.  Rows past the
+                            // end are read (at most 7 past a scratch's CAP rows, in the MAXTR pooled
+                            // rows behind them) and count as 0, so that a read is one instruction.
                             static_assert(C::MAXTR >= 7, "rows read past the scratch");
                             float sum = 0.f;
-                            const float *row = stage + s0 * C::STS + cc;
-                            for (int u0 = 0; u0 < len; u0 += 8, row += 8 * C::STS) {
-                                float v[8];
 #pragma unroll
-                                for (int i = 0; i < 8; ++i) {
-                                    if constexpr (C::PAIR)
-                                        v[i] = prow_of(s0 + (u0 + i < len ? u0 + i : len - 1))[cc];
-                                    else
-                                        v[i] = row[i * C::STS];
+                            for (int seg = 0; seg < (C::PAIR ? 2 : 1); ++seg) {
+                                const int lo = C::PAIR && seg ? (s0 > CAP ? s0 : CAP) : s0;
+                                const int hi = C::PAIR && !seg ? (s0 + len < CAP ? s0 + len : CAP) : s0 + len;
+                                const float *row = prow_of(seg * CAP) + (lo - seg * CAP) * C::STS + cc;
+                                for (int u = lo; u < hi; u += 8, row += 8 * C::STS) {
+                                    float v[8];
+#pragma unroll
+                                    for (int i = 0; i < 8; ++i) v[i] = row[i * C::STS];
+#pragma unroll
+                                    for (int i = 0; i < 8; ++i) sum += u + i < hi ? v[i] : 0.f;
                                 }
-#pragma unroll
-                                for (int i = 0; i < 8; ++i) sum += u0 + i < len ? v[i] : 0.f;
                             }
                             pblk[(tr - tr0) * C::STS + cc] = sum / (float)len;  // 0 / 0 = NaN for an empty track
                         }
