@@ -168,7 +168,8 @@ __device__ __forceinline__ float silu_f32(float v) {
 // order, with the fragments of the next DEPTH - 1 steps always on their way (load(i)
 // reads one).  The fences keep that order: left to itself the compiler reads two
 // fragments, waits for both (an LDS read under load takes longer than two products)
-// and only then issues their products.  DEPTH 0: left to the compiler (for kernels
+// and only then issues their products.  d = 256, six layers, 262 144 tracks: 18.2 ->
+// 17.2 ms with three; d = 128, 500 tracks: 39.2 -> 37.6 us with four.  DEPTH 0: left to the compiler (for kernels
 // that have no registers for it).
 template <int N, int DEPTH, class Load, class Step>
 __device__ __forceinline__ void ring_products(Load load, Step step) {

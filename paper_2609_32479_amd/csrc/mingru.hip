@@ -20,7 +20,7 @@
 // A wave takes a tile of whole tracks (at most 32 hits, 16 tracks), holds the
 // tile's input rows as matrix operands in registers (hits on the rows of
 // 32x32 products), and for each 32-channel chunk and direction multiplies
-// them with the candidate block, then the gate block, of the weights, which
+// them with the gate block, then the candidate block, of the weights, which
 // stream through an LDS ring shared by the workgroup (one stage per block).
 // The accumulators hold channel cc of tile rows 16 s + q in lane (s, cc),
 // register q: two streams of 16 positions per lane half, scanned in place; a
@@ -428,7 +428,8 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                 // dir 2H + 32 ch + cc.  Beside its products the gates a = sigmoid(g), which
                 // need the gate block alone: the update adds a x and keeps 1 - a of the state.
                 // (With the gates after both blocks the fp32 layer of input 384, one wave per
-                // SIMD, kept the matrix cores busy 39 % of the time.)
+                // SIMD, kept the matrix cores busy 39 % of the time; 40 000 tracks through the
+                // fp32 model 3.35 -> 3.00 ms.)
                 constexpr int XOFF = C::MERGE ? C::BLOCK : 0;
                 float CF[SP];
                 if constexpr (!C::HALF) {
@@ -874,7 +875,9 @@ void tf_backbone_kernel(const float *__restrict__ feats, int nf, long long n_hit
                     else
                         scan_dir<false>(AX, CF, eb0, eb1, hh);
                     pcol = dir * H + 32 * ch;
-                    // every row's state to the operand area (free in this layer), row r at
+                    // every row's state to the operand area (free in this layer; writing the
+                    // wanted rows alone took a masked store and a track count per row: with
+                    // the transposing reads above 262 144 tracks 4.08 -> 3.90 ms), row r at
                     // 36 r + 32 (r / 16) floats, then for track j of the tile the forward
                     // state at its last row or the reverse state at its first
                     float *tf = reinterpret_cast<float *>(xa1);

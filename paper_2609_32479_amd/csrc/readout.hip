@@ -233,7 +233,8 @@ inline bool head16_in_lds(int d, int hidden) {
 // waves per SIMD.
 // Tile t is wave t / grid of workgroup t % grid in the first turn, so that few tiles
 // lie on different compute units.
-// 262 144 tracks of the paper's head: 168 -> 119 us (3.9 TB/s).
+// 262 144 tracks of the paper's head: 168 -> 114 us (2.7 -> 4.1 TB/s; a large
+// copy reaches 4.7).
 // LDSW: the weights in LDS; otherwise they are read from memory by each wave.
 template <int MT, bool LDSW>
 __global__ __launch_bounds__(64 * kWaves16) void tf_readout16_kernel(const float *__restrict__ states, int n, int D,

@@ -1360,7 +1360,9 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                             // in row order, eight independent reads at a time; a pair's rows lie in
                             // the scratches of its two waves, one after the other.  Rows past the
                             // end are read (at most 7 past a scratch's CAP rows, in the MAXTR pooled
-                            // rows behind them) and count as 0, so that a read is one instruction.
+                            // rows behind them) and count as 0, so that a read is one instruction
+                            // (50 000 tracks of 64 hits 2.36 -> 2.11 ms; 262 144 of 8 to 20 hits
+                            // 2.45 -> 2.40 ms).
                             static_assert(C::MAXTR >= 7, "rows read past the scratch");
                             float sum = 0.f;
 #pragma unroll
