@@ -29,7 +29,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <climits>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -255,8 +254,8 @@ __device__ __forceinline__ void mg_tile_meta(unsigned long long smask, int n, in
 template <int OP, int DIN, int H, bool LAST>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * MCfg<OP, DIN>::WAVES, 64 * MCfg<OP, DIN>::WAVES),
                           amdgpu_waves_per_eu(MCfg<OP, DIN>::WAVES / 4, MCfg<OP, DIN>::WAVES / 4)))
-void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_rows, const int *__restrict__ offsets,
-                      int n_tracks, const unsigned char *__restrict__ stages, typename Frag<OP>::E *__restrict__ Y,
+void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_rows, long long n_hits,
+                      const int *__restrict__ offsets, int n_tracks, const unsigned char *__restrict__ stages, typename Frag<OP>::E *__restrict__ Y,
                       float *__restrict__ states, int *__restrict__ err) {
     using C = MCfg<OP, DIN>;
     using F = Frag<OP>;
@@ -302,7 +301,7 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
     for (;;) {
         int k, n;
         unsigned long long smask;
-        if (!wk.next(offsets, row0, x_rows, LLONG_MAX, errbits, LAST ? states : nullptr, H, t_start, k, n, smask)) break;
+        if (!wk.next(offsets, row0, x_rows, n_hits, errbits, LAST ? states : nullptr, H, t_start, k, n, smask)) break;
         const bool work = k > 0;
         copy_stage<C>(stages, (q + C::NSLOT - 1) % S, slot_lds(q + C::NSLOT - 1), wid, lane);
 
@@ -531,22 +530,25 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
 }
 
 template <int OP, int DIN, int H, bool LAST>
-hipError_t launch_layer(const void *X, long long x_rows, const int32_t *offsets, int32_t n_tracks,
+hipError_t launch_layer(const void *X, long long x_rows, long long n_hits, const int32_t *offsets, int32_t n_tracks,
                         const unsigned char *stages, void *Y, float *states, int *err, int cu_count,
                         hipStream_t stream) {
     using C = MCfg<OP, DIN>;
     using FE = typename Frag<OP>::E;
     hipLaunchKernelGGL((tf_mingru_kernel<OP, DIN, H, LAST>), dim3(workgroups(n_tracks, cu_count)), dim3(64 * C::WAVES), 0, stream,
-                       static_cast<const FE *>(X), x_rows, offsets, (int)n_tracks, stages, static_cast<FE *>(Y), states,
+                       static_cast<const FE *>(X), x_rows, n_hits, offsets, (int)n_tracks, stages, static_cast<FE *>(Y), states,
                        err);
     return hipGetLastError();
 }
 
 template <int OP, int DIN, int H>
-hipError_t launch_last(bool last, const void *X, long long x_rows, const int32_t *offsets, int32_t n_tracks,
-                       const unsigned char *stages, void *Y, float *states, int *err, int cu_count, hipStream_t stream) {
-    return last ? launch_layer<OP, DIN, H, true>(X, x_rows, offsets, n_tracks, stages, Y, states, err, cu_count, stream)
-                : launch_layer<OP, DIN, H, false>(X, x_rows, offsets, n_tracks, stages, Y, states, err, cu_count, stream);
+hipError_t launch_last(bool last, const void *X, long long x_rows, long long n_hits, const int32_t *offsets,
+                       int32_t n_tracks, const unsigned char *stages, void *Y, float *states, int *err, int cu_count,
+                       hipStream_t stream) {
+    return last ? launch_layer<OP, DIN, H, true>(X, x_rows, n_hits, offsets, n_tracks, stages, Y, states, err, cu_count,
+                                                 stream)
+                : launch_layer<OP, DIN, H, false>(X, x_rows, n_hits, offsets, n_tracks, stages, Y, states, err, cu_count,
+                                                  stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -1239,27 +1241,27 @@ tf_status mingru_states(const float *hits, int64_t n_hits, const int32_t *offset
         switch (h->op) {
             case OP_BF16:
                 if (H == 192)
-                    e = din == 128 ? launch_last<OP_BF16, 128, 192>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                   : launch_last<OP_BF16, 384, 192>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 128 ? launch_last<OP_BF16, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
+                                   : launch_last<OP_BF16, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
                 else
-                    e = din == 32 ? launch_last<OP_BF16, 32, 64>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                  : launch_last<OP_BF16, 128, 64>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 32 ? launch_last<OP_BF16, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
+                                  : launch_last<OP_BF16, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
                 break;
             case OP_F16:
                 if (H == 192)
-                    e = din == 128 ? launch_last<OP_F16, 128, 192>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                   : launch_last<OP_F16, 384, 192>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 128 ? launch_last<OP_F16, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
+                                   : launch_last<OP_F16, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
                 else
-                    e = din == 32 ? launch_last<OP_F16, 32, 64>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                  : launch_last<OP_F16, 128, 64>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 32 ? launch_last<OP_F16, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
+                                  : launch_last<OP_F16, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
                 break;
             default:
                 if (H == 192)
-                    e = din == 128 ? launch_last<OP_F32, 128, 192>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                   : launch_last<OP_F32, 384, 192>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 128 ? launch_last<OP_F32, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
+                                   : launch_last<OP_F32, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
                 else
-                    e = din == 32 ? launch_last<OP_F32, 32, 64>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                  : launch_last<OP_F32, 128, 64>(last, xin, rows, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 32 ? launch_last<OP_F32, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
+                                  : launch_last<OP_F32, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
                 break;
         }
         if (e != hipSuccess) return TF_EHIP;
