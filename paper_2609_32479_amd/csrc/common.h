@@ -143,25 +143,33 @@ inline Bf16Parts bf16_parts(float v) {
     return {{uint16_t(h >> 16), uint16_t(m >> 16), uint16_t(bits(r - value(m)) >> 16)}};
 }
 
-// e = exp(x) for |x| <= 80 in fp32: the hardware's exp2 (1 ulp) of the rounded product
-// x log2(e), times 1 + ln(2) (its rounding error); and 1 / d for 1 <= d <= 2^126: the
-// hardware's reciprocal (1 ulp) with one Newton step.  6 and 3 instructions; the
-// library's forms cover ranges that a clamped argument cannot reach and take
-// about 14 and 11.
+// exp(x) for |x| <= 80 in fp32: x log2(e) = p + l with the product's and log2(e)'s
+// rounding errors in l, p = n + (p - n) with n the nearest whole number (in the low bits
+// of q), the hardware's exp2 of (p - n) + l, and n added to the exponent bits.
+// 1 / d for 1 <= d <= 2^126: the hardware's reciprocal (1 ulp) and one Newton step, whose
+// last operation rounds a value right to 2^-45: the correctly rounded quotient.
+// Against 64 bits over |x| <= 80 (4 M arguments) exp is 0.83 ulp off at most and 0.30 in
+// the root mean square, the library's figures to the last digit (with exp2 of the
+// unreduced product 1.23 and 0.41); of 4 M quotients 1 / (1 + e) none differs from the
+// division's.  9 and 3 instructions; the library's forms also cover ranges that a
+// clamped argument cannot reach and take about 14 and 11.
 __device__ __forceinline__ float exp_clamped(float x) {
-    constexpr float kLog2eLo = float(1.4426950408889634 - double(kLog2e)), kLn2 = 0.6931471805599453f;
-    const float p = x * kLog2e;
-    const float l = fmaf(x, kLog2eLo, fmaf(x, kLog2e, -p));
-    const float e = __builtin_amdgcn_exp2f(p);
-    return fmaf(e * kLn2, l, e);
+#pragma clang fp contract(off)  // (p is the rounded product everywhere)
+    constexpr float kLog2eLo = float(1.4426950408889634 - double(kLog2e)), kRound = 0x1.8p23f;
+    const float q = fmaf(x, kLog2e, kRound), p = x * kLog2e;
+    const float f = (p - (q - kRound)) + fmaf(x, kLog2eLo, fmaf(x, kLog2e, -p));
+    return __uint_as_float(__float_as_uint(__builtin_amdgcn_exp2f(f)) + (__float_as_uint(q) << 23));
 }
 __device__ __forceinline__ float rcp_clamped(float d) {
     const float r = __builtin_amdgcn_rcpf(d);
     return fmaf(fmaf(-d, r, 1.0f), r, r);
 }
-// v sigmoid(v), the exponent clamped (the change is below exp(-80)).
+// v sigmoid(v) = v / (1 + exp(-v)), the exponent clamped (the change is below exp(-80)
+// |v|), the quotient with a residual step, which rounds it as the division would.
 __device__ __forceinline__ float silu_f32(float v) {
-    return v * rcp_clamped(1.0f + exp_clamped(-__builtin_amdgcn_fmed3f(v, -80.0f, 80.0f)));
+    const float d = 1.0f + exp_clamped(-__builtin_amdgcn_fmed3f(v, -80.0f, 80.0f)), r = rcp_clamped(d);
+    const float q = v * r;
+    return fmaf(fmaf(-d, q, v), r, q);
 }
 
 // N products in a row whose weight fragments come from LDS: step(i, fragment i) for i in

@@ -25,7 +25,7 @@ def test_tracks_past_the_hits_are_refused(name, fused, cut):
     M = tf.MinGRU(ts.make_mingru_weights(w), w.n_layers, w.d_model, w.hidden, tf.MODE_FOR_WEIGHTS[w.dtype], w.n_features)
     if fused is not None:
         M.set_fused(fused)
-    n, good = 400, 331
+    n, good = 6000, 4731
     hits, offs = ts.make_tracks(w, n_tracks=n)
     if w.n_features:
         lo, hi = ts.feature_bounds(w)
