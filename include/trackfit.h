@@ -48,7 +48,9 @@ typedef enum { TF_FP32 = 0, TF_BF16 = 1, TF_BF16_F16ACT = 2 } tf_dtype;
  * gate, both scan states, the residual stream, the mean pool and the outputs
  * are fp32 in every mode (Sec. Kernel adaptation: reduced-precision
  * projections, fp32 recurrence).  The modes differ in the GEMM operands:
- * TF_FP32         fp32 weights and activations.
+ * TF_FP32         fp32 weights and activations, each multiplied as three bf16
+ *                 parts (products to 2^-24, 2^-23 with the rounding) and summed
+ *                 in fp32.
  * TF_BF16         bf16 weights; the normalised activations and the scan
  *                 outputs are rounded to bf16 as GEMM operands.
  * TF_BF16_F16ACT  weights converted to fp16 operands, activations rounded
@@ -316,7 +318,7 @@ tf_status tf_decode_tracks(const float *states, int32_t n_tracks, const double *
  * Eq. (2) from each track's first hit and from its last (zero initial state),
  * and [f; b] (2H values per hit) feeds the next layer; no normalisation or
  * residual inside.
- * Number types as for tf_config.dtype: fp32 throughout, or 16-bit matrix
+ * Number types as for tf_config.dtype: fp32 (products as there), or 16-bit matrix
  * operands (weights bf16, activations bf16 or fp16) with fp32 accumulation,
  * gates and recurrence.
  */

@@ -45,6 +45,7 @@ template <> struct Frag<OP_BF16> {
     static __device__ __forceinline__ f32x16 mma(T a, T b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ void mma(T a, T b, f32x16 &c, f32x16 &) { c = mma(a, b, c); }
     static __device__ __forceinline__ f32x4 mma16(T a, T b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     }
@@ -59,6 +60,7 @@ template <> struct Frag<OP_F16> {
     static __device__ __forceinline__ f32x16 mma(T a, T b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ void mma(T a, T b, f32x16 &c, f32x16 &) { c = mma(a, b, c); }
     static __device__ __forceinline__ f32x4 mma16(T a, T b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
     }
@@ -67,42 +69,53 @@ template <> struct Frag<OP_F16> {
         return __builtin_convertvector(f, f16x8);
     }
 };
-// fp32 operands on the bf16 matrix cores.  An fp32 value is exactly h + m + l, three
-// bf16 values of 8 significant bits each (h cut off, so that no finite value
-// overflows; m rounded, so that l and the dropped products have either sign), and
-// a product is taken as its six largest part
-// products; the three dropped ones (m l, l m, l l) are below 2^-23 of it, and
-// with a rounding of the sum every 16 terms instead of every two (the depth of the
-// fp32 matrix instruction) the error against 64 bits is smaller: 4.2e-7 against
-// 4.6e-7 (2-norm, four layers of 128), 1.8e-7 against 2.2e-7 (64), 3.2e-7 against
-// 4.2e-7 (minGRU).  (Every part cut off: 5.6e-7, as the dropped products then add
-// up.)  Six bf16 products of depth 16 take 192 cycles where eight fp32 ones of
-// depth 2 take 512: 65 536 tracks through the d = 128 encoder 4.75 -> 2.99 ms,
-// 40 000 through the minGRU 5.78 -> 3.60 ms.
+// fp32 operands on the bf16 matrix cores (the splitting into exact parts that
+// extended-precision sums use).  An fp32 value of magnitude 2^-110 or more is exactly
+// h + m + l, three bf16 values of 8 significant bits each, h and m rounded, so that |m|
+// is at most 2^-8 and |l| 2^-17 of a significand (below 2^-110 l, and then m, lose bits
+// that are below bf16's smallest subnormal: at most 2^-134).  A product is taken as its
+// six largest part products; of the three left out, m l and l m are together at most
+// 2^-24 of the product, l l far below.
+// The matrix cores cut a sum off where they add a product to it (a lone product
+// added to its own small parts is up to 2 units of 2^-24 off, the fp32 instruction 1), so
+// the products h h have a sum of their own, in which few terms are exact, the small ones
+// another, and one fp32 addition rounds the two: a row of one term is 0.435 units off in
+// the root mean square (fp32 instruction 0.424) and at most 2 (1), of two terms 0.37
+// (0.43), of eight 0.25 (0.46), of 128 0.15 (0.47).  In one sum and with h cut off a
+// row of one term was 0.69 off and up to 4.2, of eight terms 0.95.  Two-norm errors
+// against 64 bits: 65 536 tracks, four layers of 128: 1.9e-7 (one sum 2.9e-7); the
+// minGRU of 40 000: 1.5e-7 (3.2e-7).
+// Cycles of 16 terms: 192 against 512 of the fp32 instruction.  65 536 tracks through
+// the d = 128 encoder take 2.80 ms, 40 000 through the minGRU 3.06 (one sum 2.72 and 2.96,
+// the fp32 instruction 5.49 and 6.77).  All eight products above 2^-30, with parts cut
+// off: 0.424 units for one term, but 3.60 and 3.81 ms.
 struct bf16x8x3 {
     bf16x8 h, m, l;
 };
 template <> struct Frag<OP_F32> {
     typedef bf16x8x3 T;
     typedef float E;
-    static __device__ __forceinline__ f32x16 mma(const T &a, const T &b, f32x16 c) {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, c, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, c, 0, 0, 0);
+    // (named by the pipelined layers, which no fp32 kernel has)
+    static __device__ f32x16 mma(const T &a, const T &b, f32x16 c);
+    // c += the large products, s += the small ones
+    static __device__ __forceinline__ void mma(const T &a, const T &b, f32x16 &c, f32x16 &s) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, s, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, c, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, s, 0, 0, 0);
     }
-    // The same in two sums, products of one taking turns with the other's: for a wave
-    // that has the SIMD to itself, whose dependent products run at 44 cycles each
-    // instead of 32.
-    static __device__ __forceinline__ void mma2(const T &a, const T &b, f32x16 &c, f32x16 &d) {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, c, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, d, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, c, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, d, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, c, 0, 0, 0);
-        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, d, 0, 0, 0);
+    // The same with the small products in two sums, which take turns: for a wave that
+    // has the SIMD to itself, whose dependent products run at 44 cycles each instead of
+    // 32.
+    static __device__ __forceinline__ void mma(const T &a, const T &b, f32x16 &c, f32x16 &s, f32x16 &t) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, s, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, t, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, s, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, t, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, s, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, c, 0, 0, 0);
     }
     static __device__ __forceinline__ T pack(const float *v) {
         typedef float f2 __attribute__((ext_vector_type(2)));
@@ -110,12 +123,13 @@ template <> struct Frag<OP_F32> {
         u32x4 h, m, l;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const unsigned u0 = __float_as_uint(v[2 * i]), u1 = __float_as_uint(v[2 * i + 1]);
-            const f2 r = {v[2 * i] - __uint_as_float(u0 & 0xffff0000u), v[2 * i + 1] - __uint_as_float(u1 & 0xffff0000u)};
-            const unsigned mm = __builtin_bit_cast(unsigned, __builtin_convertvector(r, b2));
-            const float s0 = r[0] - __uint_as_float(mm << 16), s1 = r[1] - __uint_as_float(mm & 0xffff0000u);
-            h[i] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the high halves of both
-            m[i] = mm;
+            const f2 x = {v[2 * i], v[2 * i + 1]};
+            const unsigned hb = __builtin_bit_cast(unsigned, __builtin_convertvector(x, b2));
+            const f2 r = {x[0] - __uint_as_float(hb << 16), x[1] - __uint_as_float(hb & 0xffff0000u)};
+            const unsigned mb = __builtin_bit_cast(unsigned, __builtin_convertvector(r, b2));
+            const float s0 = r[0] - __uint_as_float(mb << 16), s1 = r[1] - __uint_as_float(mb & 0xffff0000u);
+            h[i] = hb;
+            m[i] = mb;
             l[i] = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);
         }
         return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
@@ -136,10 +150,11 @@ inline Bf16Parts bf16_parts(float v) {
         __builtin_memcpy(&x, &u, 4);
         return x;
     };
-    const uint32_t h = bits(v) & 0xffff0000u;
+    // to the nearest bf16, ties to even
+    auto near = [](uint32_t u) { return (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u; };
+    const uint32_t h = near(bits(v));
     const float r = v - value(h);
-    uint32_t m = bits(r);
-    m = (m + 0x7fffu + ((m >> 16) & 1u)) & 0xffff0000u;
+    const uint32_t m = near(bits(r));
     return {{uint16_t(h >> 16), uint16_t(m >> 16), uint16_t(bits(r - value(m)) >> 16)}};
 }
 
@@ -165,11 +180,12 @@ __device__ __forceinline__ float rcp_clamped(float d) {
     return fmaf(fmaf(-d, r, 1.0f), r, r);
 }
 // v sigmoid(v) = v / (1 + exp(-v)), the exponent clamped (the change is below exp(-80)
-// |v|), the quotient with a residual step, which rounds it as the division would.
+// |v|), the quotient with a residual step, which rounds it as the division would (an
+// infinite quotient has none).
 __device__ __forceinline__ float silu_f32(float v) {
     const float d = 1.0f + exp_clamped(-__builtin_amdgcn_fmed3f(v, -80.0f, 80.0f)), r = rcp_clamped(d);
     const float q = v * r;
-    return fmaf(fmaf(-d, q, v), r, q);
+    return fabsf(q) < __builtin_inff() ? fmaf(fmaf(-d, q, v), r, q) : q;
 }
 
 // N products in a row whose weight fragments come from LDS: step(i, fragment i) for i in
@@ -177,8 +193,8 @@ __device__ __forceinline__ float silu_f32(float v) {
 // reads one).  The fences keep that order: left to itself the compiler reads two
 // fragments, waits for both (an LDS read under load takes longer than two products)
 // and only then issues their products.  d = 256, six layers, 262 144 tracks: 18.2 ->
-// 17.2 ms with three; d = 128, 500 tracks: 39.2 -> 37.6 us with four.  DEPTH 0: left to the compiler (for kernels
-// that have no registers for it).
+// 17.2 ms with three; d = 128, 500 tracks: 39.2 -> 37.6 us with four.  DEPTH 0: left to
+// the compiler (for kernels that have no registers for it).
 template <int N, int DEPTH, class Load, class Step>
 __device__ __forceinline__ void ring_products(Load load, Step step) {
     if constexpr (DEPTH == 0) {

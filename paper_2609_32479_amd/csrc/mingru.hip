@@ -369,9 +369,9 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
         // its product, and one wave per SIMD waits out the latency twice a k-step), and
         // the vector work is spread between the products, as a wave issues in order.
         auto products = [&](f32x16 &acc, int off, auto beside) {
-            f32x16 odd;
+            f32x16 small, small2;  // fp32: the small part products' sums (see Frag<OP_F32>)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = odd[i] = 0.f;
+            for (int i = 0; i < 16; ++i) acc[i] = small[i] = small2[i] = 0.f;
 #pragma unroll
             for (int sp = 0; sp < C::SPB; ++sp) {
                 if (sp > 0) advance(false);
@@ -392,9 +392,9 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                             const FT wc = wn;
                             if (kl + 1 < C::KPS) wn = wf[(kl + 1) * 64];
                             if constexpr (C::WAVES == 4)
-                                F::mma2(xa[ks], wc, acc, odd);
+                                F::mma(xa[ks], wc, acc, small, small2);
                             else
-                                acc = F::mma(xa[ks], wc, acc);
+                                F::mma(xa[ks], wc, acc, small);
                             beside(ks);
                             __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // the next k-step's LDS reads
 #pragma unroll
@@ -408,7 +408,8 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                     __builtin_amdgcn_s_setprio(0);
                 }
             }
-            if constexpr (C::WAVES == 4 && !C::HALF) acc += odd;
+            if constexpr (C::WAVES == 4 && !C::HALF) small += small2;
+            if constexpr (!C::HALF) acc += small;
         };
 
         // ---- chunks of 32 hidden channels, forward then reverse direction

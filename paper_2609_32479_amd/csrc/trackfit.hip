@@ -108,7 +108,11 @@ struct KCfg {
     // (row k = channel k of the chunk's [f; b], CAP slots, swizzled by fb_off)
     static constexpr int FBS = HALF ? CAP : 68;  // row stride of [f; b] (elements)
     static constexpr int STS = 33;               // row stride of the pooling scratch (floats)
-    static constexpr int FB_BYTES = HALF ? (64 * CAP + (HT_ == 1 ? 64 : 0)) * EB : CAP * FBS * EB;
+    // fp32, d = 128: the buffer also takes the split operands of its KS2 k-steps
+    static constexpr bool FBP = !HALF && D > 64;
+    static constexpr int FB_BYTES = HALF  ? (64 * CAP + (HT_ == 1 ? 64 : 0)) * EB
+                                    : FBP ? cmax(CAP * FBS * EB, HT_ * KS2 * FRAG)
+                                          : CAP * FBS * EB;
     static constexpr int POOL_BYTES = CAP * STS * 4 + MAXTR * STS * 4;
     static constexpr int WAVE_BYTES = round_up(cmax(FB_BYTES, POOL_BYTES), 16) + 4 * TMAXTR * 4;
     static constexpr int EMB_BYTES = D * 16;
@@ -124,6 +128,7 @@ struct KCfg {
     static constexpr int NIN = HALF ? 1 : 2;                 // stages of a chunk's input projection
     static constexpr int NOUT = HALF || MT < 2 ? 1 : 2;      // stages of its output projection
     static constexpr int MPO = MT / NOUT;                    // channel blocks of such a stage
+    static_assert(HALF || FBP || MPO == 1, "operands split once per stage");
     static constexpr int G1_FR = 2 / NIN * KS1;  // (candidate +) gate fragments of a stage
     static constexpr int G2_FR = MPO * KS2;      // output-projection fragments of a stage
     static constexpr int G1_BYTES = G1_FR * FRAG + 64 * 4;  // + bx[32], bg[32] (fp32: one of them)
@@ -469,6 +474,22 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
         return buf[lane];
     };
 
+    // fp32: the sums of the small part products (see Frag<OP_F32>)
+    auto zero_small = [&](f32x16(&v)[HT]) {
+        if constexpr (!C::HALF) {
+#pragma unroll
+            for (int nt = 0; nt < HT; ++nt)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) v[nt][q] = 0.f;
+        }
+    };
+    auto add_small = [&](f32x16(&c)[HT], const f32x16(&v)[HT]) {
+        if constexpr (!C::HALF) {
+#pragma unroll
+            for (int nt = 0; nt < HT; ++nt) c[nt] += v[nt];
+        }
+    };
+
     for (;;) {
         int k, n;                  // tracks and hit rows of the tile
         unsigned long long smask;  // tile rows that start a track
@@ -559,7 +580,8 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
             } else {
             // Fourier front end, part 1: the normalised features u = (x - lo) * (1 / (hi - lo))
             // (each step rounded to fp32) of hit slot 32 nt + cc to the wave's scratch, lane half
-            // hh taking features 8 hh .. 8 hh + 7; r starts at the projection's bias
+            // hh taking features 8 hh .. 8 hh + 7; r starts at the projection's bias (fp32: set
+            // after the products)
             const float *fe = reinterpret_cast<const float *>(smem);  // bias [D], lo [16], inv [16]
             float *us = stage;                                        // [CAP][kUStride]
             const int nf = P.n_feat;
@@ -578,10 +600,12 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     const int f = 8 * h2 + e;
                     if (f < nf) us[sl * kUStride + f] = hp ? (hp[f] - fe[D + f]) * fe[D + kMaxFeat + f] : 0.f;
                 }
+                if constexpr (C::HALF) {
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
+                    for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) r[m][nt][q] = fe[32 * m + 8 * (q >> 2) + 4 * h2 + (q & 3)];
+                        for (int q = 0; q < 16; ++q) r[m][nt][q] = fe[32 * m + 8 * (q >> 2) + 4 * h2 + (q & 3)];
+                }
             }
             wave_lds_sync();  // the features are in the scratch
             }
@@ -592,6 +616,12 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
             // projection), formed in registers: sin or cos of pi 2^s u_f
             const float *us = stage;
             const int kf = 32 * P.n_feat / K;  // k-steps of the projection
+            f32x16 large[MT][HT], small[MT][HT];  // fp32: the products' sums
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                zero_small(large[m]);
+                zero_small(small[m]);
+            }
             FT cnext[HT];  // the cosines that the k-step after an even one takes
 #pragma unroll
             for (int nt = 0; nt < HT; ++nt) cnext[nt] = FT{};
@@ -653,12 +683,26 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         for (int m = 0; m < MT; ++m) {
                             const FT a = wfr[(kl * MT + m) * 64 + lane];
 #pragma unroll
-                            for (int nt = 0; nt < HT; ++nt) r[m][nt] = F::mma(a, bv[nt], r[m][nt]);
+                            for (int nt = 0; nt < HT; ++nt)
+                                F::mma(a, bv[nt], C::HALF ? r[m][nt] : large[m][nt], small[m][nt]);
                         }
                     }
                     __builtin_amdgcn_s_setprio(0);
                 }
                 advance(false);
+            }
+            if constexpr (!C::HALF) {
+                const float *fe = reinterpret_cast<const float *>(smem);
+                if (work) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) {
+                            const float bv = fe[32 * m + 8 * (q >> 2) + 4 * hh + (q & 3)];
+#pragma unroll
+                            for (int nt = 0; nt < HT; ++nt) r[m][nt][q] = (large[m][nt][q] + small[m][nt][q]) + bv;
+                        }
+                }
             }
         }
 
@@ -718,13 +762,16 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     const FT *wf = reinterpret_cast<const FT *>(slot());
                     const float *bias = reinterpret_cast<const float *>(slot() + C::G1_FR * C::FRAG);
                     bgv = bias[C::HALF ? 32 + cc : cc];  // -log2(e) b in the 16-bit modes
+                    f32x16 small[HT];
+                    zero_small(small);
                     __builtin_amdgcn_s_setprio(1);
                     ring_products<KS1, kRing>([&](int i) -> FT { return wf[((C::HALF ? KS1 : 0) + i) * 64 + lane]; },
                                               [&](int i, const FT &b) {
 #pragma unroll
                                                   for (int nt = 0; nt < HT; ++nt)
-                                                      gx[nt] = F::mma(yf[nt][i], b, gx[nt]);
+                                                      F::mma(yf[nt][i], b, gx[nt], small[nt]);
                                               });
+                    add_small(gx, small);
                     __builtin_amdgcn_s_setprio(0);
                 }
                 if constexpr (C::NIN == 2) advance(false);  // the candidate's stage
@@ -750,16 +797,19 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     // with it.)
                     constexpr bool BESIDE = C::HALF && HT == 1 && OUTM == OUT_HEAD;
                     constexpr int NE = HT * 16;
+                    f32x16 small[HT];
+                    zero_small(small);
                     __builtin_amdgcn_s_setprio(1);
                     ring_products<KS1, kRing>([&](int i) -> FT { return wf[i * 64 + lane]; },
                                               [&](int ks, const FT &bx) {
 #pragma unroll
-                        for (int nt = 0; nt < HT; ++nt) ax[nt] = F::mma(yf[nt][ks], bx, ax[nt]);
+                        for (int nt = 0; nt < HT; ++nt) F::mma(yf[nt][ks], bx, ax[nt], small[nt]);
                         if constexpr (BESIDE) {
 #pragma unroll
                             for (int i = ks * NE / KS1; i < (ks + 1) * NE / KS1; ++i) gate(i);
                         }
                     });
+                    add_small(ax, small);
                     __builtin_amdgcn_s_setprio(0);
                     // the update adds a x and keeps cf = 1 - a of the state
                     float AX[NE], CF[NE];
@@ -884,48 +934,74 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         if (jo == 0) wave_lds_sync();  // this wave's [f; b] stores are visible
                         __builtin_amdgcn_s_setprio(1);
                         const FT *wo = reinterpret_cast<const FT *>(sl);
-                        f32x16 part[C::HALF ? 1 : C::MPO][HT];
-                        if constexpr (!C::HALF) {
+                        if constexpr (C::HALF) {
+                            FT bfr[HT];
+                            ring_products<KS2 * C::MPO, kRing>(
+                                [&](int i) -> FT { return wo[((i % C::MPO) * KS2 + i / C::MPO) * 64 + lane]; },
+                                [&](int i, const FT &a) {
+                                    const int kk = i / C::MPO, m = i % C::MPO;
 #pragma unroll
-                            for (int m = 0; m < C::MPO; ++m)
+                                    for (int nt = 0; nt < HT; ++nt) {
+                                        if (m == 0) bfr[nt] = fb_tr_frag<C, FT>(ws, nt, kk, hh, cc);
+                                        r[m][nt] = F::mma(a, bfr[nt], r[m][nt]);
+                                    }
+                                });
+                        } else {
+                            auto fb_row8 = [&](int nt, int kk) {
+                                return reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(ws) +
+                                                                       (32 * nt + cc) * C::FBS + kk * K + hh * KL);
+                            };
+                            auto split = [&](const f32x4 &v0, const f32x4 &v1) -> FT {
+                                const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                                return F::pack(v);
+                            };
+                            // more than one channel block per stage: the operands are split once
+                            // per chunk and go back, in the place of the buffer, as the blocks read
+                            // them, since one block at a time leaves the registers for two sums
+                            FT *ops = reinterpret_cast<FT *>(ws) + lane;
+                            if constexpr (C::FBP) {
+                                if (jo == 0) {
+                                    f32x4 v[HT][KS2][2];
+#pragma unroll
+                                    for (int nt = 0; nt < HT; ++nt)
+#pragma unroll
+                                        for (int kk = 0; kk < KS2; ++kk) {
+                                            v[nt][kk][0] = fb_row8(nt, kk)[0];
+                                            v[nt][kk][1] = fb_row8(nt, kk)[1];
+                                        }
+                                    wave_lds_sync();
+#pragma unroll
+                                    for (int nt = 0; nt < HT; ++nt)
+#pragma unroll
+                                        for (int kk = 0; kk < KS2; ++kk) {
+                                            ops[(nt * KS2 + kk) * 64] = split(v[nt][kk][0], v[nt][kk][1]);
+                                            __builtin_amdgcn_sched_barrier(0);  // (registers)
+                                        }
+                                    wave_lds_sync();
+                                }
+                            }
+#pragma unroll
+                            for (int m = 0; m < C::MPO; ++m) {
+                                f32x16 part[HT], small[HT];
 #pragma unroll
                                 for (int nt = 0; nt < HT; ++nt)
 #pragma unroll
-                                    for (int q = 0; q < 16; ++q) part[m][nt][q] = 0.f;
-                        }
-                        FT bfr[HT];
-                        ring_products<KS2 * C::MPO, kRing>(
-                            [&](int i) -> FT { return wo[((i % C::MPO) * KS2 + i / C::MPO) * 64 + lane]; },
-                            [&](int i, const FT &a) {
-                                const int kk = i / C::MPO, m = i % C::MPO;
-                                if (m == 0) {
+                                    for (int q = 0; q < 16; ++q) part[nt][q] = small[nt][q] = 0.f;
+#pragma unroll
+                                for (int kk = 0; kk < KS2; ++kk) {
+                                    const FT a = wo[(m * KS2 + kk) * 64 + lane];
 #pragma unroll
                                     for (int nt = 0; nt < HT; ++nt) {
-                                        if constexpr (C::HALF) {
-                                            bfr[nt] = fb_tr_frag<C, FT>(ws, nt, kk, hh, cc);
-                                        } else {
-                                            const f32x4 *fb = reinterpret_cast<const f32x4 *>(
-                                                reinterpret_cast<const float *>(ws) + (32 * nt + cc) * C::FBS + kk * K +
-                                                hh * KL);
-                                            const f32x4 v0 = fb[0], v1 = fb[1];
-                                            const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                                            bfr[nt] = F::pack(v);
-                                        }
+                                        if constexpr (C::FBP)
+                                            F::mma(a, ops[(nt * KS2 + kk) * 64], part[nt], small[nt]);
+                                        else
+                                            F::mma(a, split(fb_row8(nt, kk)[0], fb_row8(nt, kk)[1]), part[nt], small[nt]);
                                     }
+                                    if constexpr (C::FBP) __builtin_amdgcn_sched_barrier(0);
                                 }
 #pragma unroll
-                                for (int nt = 0; nt < HT; ++nt) {
-                                    if constexpr (C::HALF)
-                                        r[m][nt] = F::mma(a, bfr[nt], r[m][nt]);
-                                    else
-                                        part[m][nt] = F::mma(a, bfr[nt], part[m][nt]);
-                                }
-                            });
-                        if constexpr (!C::HALF) {
-#pragma unroll
-                            for (int m = 0; m < C::MPO; ++m)
-#pragma unroll
-                                for (int nt = 0; nt < HT; ++nt) r[jo * C::MPO + m][nt] += part[m][nt];
+                                for (int nt = 0; nt < HT; ++nt) r[jo * C::MPO + m][nt] += part[nt] + small[nt];
+                            }
                         }
                         if (ch == NCH - 1) {
                             const float *bo = reinterpret_cast<const float *>(sl + C::G2_FR * C::FRAG);
@@ -1294,6 +1370,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
         {  // the head re-derives its lane values (see KCfg::TIGHT)
             const int lane = C::TIGHT ? fresh_lane() : int(threadIdx.x & 63);
             const int hh = lane >> 5, cc = lane & 31;
+            f32x16 hidsm[C::HALF ? 1 : MT];  // fp32: the small part products' sums
             f32x16 hid[C::HEAD16 ? 1 : MT];  // 32x32 head: units 32 m + 8 (q/4) + 4 hh + q%4 of track cc
             f32x4 hq[C::HEAD16 ? C::UB : 1];  // 16x16 head: units 16 ub + 4 hg + i of track hcol
             const int hcol = lane & 15, hg = lane >> 4;
@@ -1309,7 +1386,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) hid[m][q] = 0.f;
+                    for (int q = 0; q < 16; ++q) hid[m][q] = hidsm[C::HALF ? 0 : m][q] = 0.f;
             }
             const int prow = cc < MAXTR ? cc : MAXTR - 1;  // columns past the tile's tracks repeat the last
             const bool hw = work && OUTM == OUT_HEAD;  // rows to pool
@@ -1405,7 +1482,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
 #pragma unroll
                                 for (int mu = 0; mu < MT; ++mu) {
                                     const FT a = w1[((bl * KPB + kb) * MT + mu) * 64 + lane];
-                                    hid[mu] = F::mma(a, b_hi, hid[mu]);
+                                    F::mma(a, b_hi, hid[mu], hidsm[C::HALF ? 0 : mu]);
                                     if constexpr (C::HALF) hid[mu] = F::mma(a, b_lo, hid[mu]);
                                 }
                             }
@@ -1428,7 +1505,8 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                         // bias and SiLU: lane (hh, cc) holds units 32 mu + 8 (q/4) + 4 hh + (q%4) of track cc
                         const float *b1 = reinterpret_cast<const float *>(slot() + C::KSPS * MT * C::FRAG);
 #pragma unroll
-                        for (int mu = 0; mu < MT; ++mu)
+                        for (int mu = 0; mu < MT; ++mu) {
+                            if constexpr (!C::HALF) hid[mu] += hidsm[mu];
 #pragma unroll
                             for (int q = 0; q < 16; ++q) {
                                 const float v = hid[mu][q] + b1[32 * mu + 8 * (q >> 2) + 4 * hh + (q & 3)];
@@ -1440,6 +1518,7 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                                     sv = silu_f32(v);
                                 hid[mu][q] = sv;
                             }
+                        }
                     }
                 }
                 advance(false);
@@ -1483,9 +1562,9 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
             } else if (hc) {
                 const FT *w2 = reinterpret_cast<const FT *>(slot());
                 const float *b2 = reinterpret_cast<const float *>(slot() + KS1 * C::FRAG);
-                f32x16 o;
+                f32x16 o, osm;
 #pragma unroll
-                for (int q = 0; q < 16; ++q) o[q] = 0.f;
+                for (int q = 0; q < 16; ++q) o[q] = osm[q] = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < KS1; ++ks) {
                     float v[8];
@@ -1494,9 +1573,10 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     FT b_hi, b_lo;
                     split_operand<F>(v, b_hi, b_lo);
                     const FT a = w2[ks * 64 + lane];
-                    o = F::mma(a, b_hi, o);
+                    F::mma(a, b_hi, o, osm);
                     if constexpr (C::HALF) o = F::mma(a, b_lo, o);
                 }
+                if constexpr (!C::HALF) o += osm;
                 if (cc < k) {
                     float *op = out + (size_t)t_id[cc] * 5;
                     if (hh == 0) {

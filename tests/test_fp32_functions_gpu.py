@@ -71,3 +71,16 @@ def test_head_silu(span):
     xg = torch.from_numpy(x).cuda()
     lib = (xg / (1.0 + torch.exp(-xg))).cpu().numpy()
     _check(out[:, 0], lib, x.astype(np.float64) / (1.0 + np.exp(-x.astype(np.float64))))
+
+
+def test_head_silu_of_infinity():
+    """An infinite argument of the readout head's SiLU (a bias) stays infinite, with its sign."""
+    import paper_2609_32479_amd as tf
+    st, sd = torch.ones((40, 64), device="cuda"), torch.zeros((40, 5), dtype=torch.float64, device="cuda")
+    for s in (np.inf, -np.inf):
+        blob = np.zeros(tf.readout_blob_size(32, 32), np.float32)
+        o = 64 + 32 * 64
+        blob[o] = s                             # b1[0]
+        blob[o + 32:o + 32 + 35 * 32:32] = 1.0  # W2[:, 0]
+        _, q = tf.decode_tracks(st, sd, tf.Readout(blob, 32, 32, "fp32"), quantiles=True)
+        assert (q == s).all()
