@@ -22,9 +22,11 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 // sum of three bf16 parts (see Frag<OP_F32>).  OP_BF16: bf16 weights and bf16 activation
 // operands (v_mfma_f32_32x32x16_bf16).  OP_F16: weights converted to fp16
 // (exact for bf16 values in the fp16 normal range) and fp16 activation
-// operands (v_mfma_f32_32x32x16_f16).
-// Accumulation is fp32 in all three.
-enum { OP_F32 = 0, OP_BF16 = 1, OP_F16 = 2 };
+// operands (v_mfma_f32_32x32x16_f16).  OP_F32W: fp32 as OP_F32, the same stored weights,
+// multiplied by the fp32 instruction (see Frag<OP_F32W>).
+// Accumulation is fp32 in all four.
+enum { OP_F32 = 0, OP_BF16 = 1, OP_F16 = 2, OP_F32W = 3 };
+constexpr bool is_half(int op) { return op == OP_BF16 || op == OP_F16; }
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kRmsEps = 1e-6f;
@@ -135,7 +137,77 @@ template <> struct Frag<OP_F32> {
         return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
     }
 };
-// The same split on the host (the weights): the parts' bf16 bits.
+// fp32 operands that may be infinite, or so large that part products overflow: h m and
+// h l of an infinite h are infinite or NaN where the product is neither, and parts of
+// different signs overflow to different infinities.  They are put together again and
+// multiplied by the fp32 instruction (8 of 64 cycles for 16 terms).
+// It runs where weights or operands are beyond the limits here, below which no sum of
+// up to 384 products can overflow: a handle with such weights takes it throughout, and
+// the places that see operands without a bound (the minGRU's input rows, the head's
+// pooled and hidden values) look for them, a comparison per eight values.  The
+// normalised stream is at most sqrt(d), the states then stay below 2^61 with weights and
+// biases below the limits, and sines and cosines are at most 1.
+constexpr float kWideWeight = 0x1p27f, kWideBias = 0x1p60f, kWideOperand = 0x1p90f;
+template <> struct Frag<OP_F32W> {
+    typedef bf16x8x3 T;
+    typedef float E;
+    static __device__ __forceinline__ float value(const T &x, int e) {
+        return ((float)x.l[e] + (float)x.m[e]) + (float)x.h[e];
+    }
+    static __device__ __forceinline__ f32x16 mma(const T &a, const T &b, f32x16 c) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(value(a, e), value(b, e), c, 0, 0, 0);
+        return c;
+    }
+    static __device__ __forceinline__ void mma(const T &a, const T &b, f32x16 &c, f32x16 &) { c = mma(a, b, c); }
+    // (h cut off, so that no finite value becomes infinite; no further parts of infinity)
+    static __device__ __forceinline__ T pack(const float *v) {
+        T x;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float h = __uint_as_float(__float_as_uint(v[e]) & 0xffff0000u);
+            const float r = fabsf(v[e]) == __builtin_inff() ? 0.0f : v[e] - h;
+            const float m = __uint_as_float(__float_as_uint(r) & 0xffff0000u);
+            x.h[e] = (__bf16)h;
+            x.m[e] = (__bf16)m;
+            x.l[e] = (__bf16)(r - m);
+        }
+        return x;
+    }
+};
+// The larger of m and the eight values' magnitudes (NaN, which stays NaN in the part
+// products, does not count).
+__device__ __forceinline__ float max_abs(float m, const float *v) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[e]));
+    return m;
+}
+// The operand's columns or rows (bit i: lanes i and i + 32) that hold a magnitude beyond
+// kWideOperand.
+__device__ __forceinline__ unsigned wide_mask(float magnitude) {
+    const unsigned long long w = __ballot(magnitude >= kWideOperand);
+    return unsigned(w) | unsigned(w >> 32);
+}
+// The operand of this lane's values for the fp32 instruction if its column or row is
+// wide, and for the part products if not; 0 for the other, which then adds nothing (the
+// weights are finite): a track's bits do not depend on what else lies in its tile.
+__device__ __forceinline__ bf16x8x3 take_wide(float *v, bool wide) {
+    float w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        w[e] = wide ? v[e] : 0.0f;
+        v[e] = wide ? 0.0f : v[e];
+    }
+    return Frag<OP_F32W>::pack(w);
+}
+// On the host: whether any of n weights (or biases) is beyond the limit.
+inline bool any_beyond(const float *w, size_t n, float limit) {
+    for (size_t i = 0; i < n; ++i)
+        if (!(__builtin_fabsf(w[i]) < limit)) return true;
+    return false;
+}
+// The split of OP_F32 on the host (the weights): the parts' bf16 bits.  From 2^127 on h is
+// cut off (rounded it might be infinite); infinity and NaN have no further parts.
 struct Bf16Parts {
     uint16_t part[3];
 };
@@ -152,7 +224,9 @@ inline Bf16Parts bf16_parts(float v) {
     };
     // to the nearest bf16, ties to even
     auto near = [](uint32_t u) { return (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u; };
-    const uint32_t h = near(bits(v));
+    if (v != v) return {{0x7fc0, 0, 0}};
+    if (__builtin_isinf(v)) return {{uint16_t(bits(v) >> 16), 0, 0}};
+    const uint32_t h = __builtin_fabsf(v) < 0x1p127f ? near(bits(v)) : bits(v) & 0xffff0000u;
     const float r = v - value(h);
     const uint32_t m = near(bits(r));
     return {{uint16_t(h >> 16), uint16_t(m >> 16), uint16_t(bits(r - value(m)) >> 16)}};

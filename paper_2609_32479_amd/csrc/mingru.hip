@@ -49,7 +49,7 @@ constexpr int kMgTPP = 4;     // waves that share a pool of tracks (pool_pack)
 
 template <int OP, int DIN>
 struct MCfg {
-    static constexpr bool HALF = OP != OP_F32;
+    static constexpr bool HALF = is_half(OP);
     static constexpr int K = 16;             // reduction depth of one product
     static constexpr int KL = K / 2;         // operand values per lane per k-step
     static constexpr int KIN = DIN / K;      // k-steps over the layer's input
@@ -255,8 +255,8 @@ template <int OP, int DIN, int H, bool LAST>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * MCfg<OP, DIN>::WAVES, 64 * MCfg<OP, DIN>::WAVES),
                           amdgpu_waves_per_eu(MCfg<OP, DIN>::WAVES / 4, MCfg<OP, DIN>::WAVES / 4)))
 void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_rows, long long n_hits,
-                      const int *__restrict__ offsets, int n_tracks, const unsigned char *__restrict__ stages, typename Frag<OP>::E *__restrict__ Y,
-                      float *__restrict__ states, int *__restrict__ err) {
+                      const int *__restrict__ offsets, int n_tracks, const unsigned char *__restrict__ stages,
+                      typename Frag<OP>::E *__restrict__ Y, float *__restrict__ states, int wide_weights, int *__restrict__ err) {
     using C = MCfg<OP, DIN>;
     using F = Frag<OP>;
     using FT = typename F::T;
@@ -308,11 +308,15 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
         // ---- tile metadata, row map and the input rows as matrix operands
         unsigned sb0 = 0, sb1 = 0, eb0 = 0, eb1 = 0, st0 = 0, st1 = 0;
         FT xa[KIN];
+        // fp32: operand rows that the fp32 instruction multiplies (see Frag<OP_F32W>); their
+        // operands here are 0
+        unsigned wide = wide_weights ? ~0u : 0u;
         if (work) {
             mg_tile_meta(smask, n, row0, lane, t_start, t_off, rowmap, sb0, sb1, eb0, eb1, st0, st1);
             // A operand: lane (s, i) holds input channels k-step K + s KL .. + KL - 1 of
             // tile row slot_to_hit(i), whose products land in accumulator row i
             const int xr = rowmap[slot_to_hit<SP>(cc)];
+            float big = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KIN; ++ks) {
                 if (xr >= 0) {
@@ -324,9 +328,17 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                         const f32x4 v1 = *reinterpret_cast<const f32x4 *>(xp + 4);
                         const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
                         xa[ks] = F::pack(v);
+                        big = max_abs(big, v);
                     }
                 } else {
                     xa[ks] = FT{};
+                }
+            }
+            if constexpr (!C::HALF) {
+                wide |= wide_mask(big);
+                if ((wide >> cc) & 1u) {
+#pragma unroll
+                    for (int ks = 0; ks < KIN; ++ks) xa[ks] = FT{};
                 }
             }
         }
@@ -384,6 +396,9 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                                                      acc = F::mma(xa[ks], w, acc);
                                                      beside(ks);
                                                  });
+                    } else if (wide_weights) {
+#pragma unroll
+                        for (int kl = 0; kl < C::KPS; ++kl) beside(sp * C::KPS + kl);
                     } else {
                         FT wn = wf[0];
 #pragma unroll
@@ -406,6 +421,22 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                         }
                     }
                     __builtin_amdgcn_s_setprio(0);
+                    if constexpr (!C::HALF) {
+                        if (wide) {
+                            const int xr = (wide >> cc) & 1u ? rowmap[slot_to_hit<SP>(cc)] : -1;
+#pragma unroll 1
+                            for (int kl = 0; kl < C::KPS; ++kl) {
+                                f32x4 v0 = {}, v1 = {};
+                                if (xr >= 0) {
+                                    const f32x4 *xp = reinterpret_cast<const f32x4 *>(
+                                        X + (size_t)xr * DIN + (sp * C::KPS + kl) * K + hh * KL);
+                                    v0 = xp[0], v1 = xp[1];
+                                }
+                                const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                                acc = Frag<OP_F32W>::mma(Frag<OP_F32W>::pack(v), wf[kl * 64], acc);
+                            }
+                        }
+                    }
                 }
             }
             if constexpr (C::WAVES == 4 && !C::HALF) small += small2;
@@ -532,23 +563,23 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
 
 template <int OP, int DIN, int H, bool LAST>
 hipError_t launch_layer(const void *X, long long x_rows, long long n_hits, const int32_t *offsets, int32_t n_tracks,
-                        const unsigned char *stages, void *Y, float *states, int *err, int cu_count,
+                        const unsigned char *stages, void *Y, float *states, int wide, int *err, int cu_count,
                         hipStream_t stream) {
     using C = MCfg<OP, DIN>;
     using FE = typename Frag<OP>::E;
     hipLaunchKernelGGL((tf_mingru_kernel<OP, DIN, H, LAST>), dim3(workgroups(n_tracks, cu_count)), dim3(64 * C::WAVES), 0, stream,
                        static_cast<const FE *>(X), x_rows, n_hits, offsets, (int)n_tracks, stages, static_cast<FE *>(Y), states,
-                       err);
+                       wide, err);
     return hipGetLastError();
 }
 
 template <int OP, int DIN, int H>
 hipError_t launch_last(bool last, const void *X, long long x_rows, long long n_hits, const int32_t *offsets,
-                       int32_t n_tracks, const unsigned char *stages, void *Y, float *states, int *err, int cu_count,
+                       int32_t n_tracks, const unsigned char *stages, void *Y, float *states, int wide, int *err, int cu_count,
                        hipStream_t stream) {
-    return last ? launch_layer<OP, DIN, H, true>(X, x_rows, n_hits, offsets, n_tracks, stages, Y, states, err, cu_count,
+    return last ? launch_layer<OP, DIN, H, true>(X, x_rows, n_hits, offsets, n_tracks, stages, Y, states, wide, err, cu_count,
                                                  stream)
-                : launch_layer<OP, DIN, H, false>(X, x_rows, n_hits, offsets, n_tracks, stages, Y, states, err, cu_count,
+                : launch_layer<OP, DIN, H, false>(X, x_rows, n_hits, offsets, n_tracks, stages, Y, states, wide, err, cu_count,
                                                   stream);
 }
 
@@ -960,6 +991,7 @@ uint16_t bits16(float x, bool bf) {
 struct tf_mingru {
     tf_mingru_config cfg{};
     int op = 0, cu_count = 0;
+    bool wide = false;                // fp32 weights beyond the limits of the part products (Frag<OP_F32W>)
     tf_weights *front = nullptr;      // the front end (an encoder handle with no layers)
     char *dmem = nullptr;             // layer stages, error word
     std::vector<const unsigned char *> stages;  // per layer
@@ -1111,6 +1143,7 @@ extern "C" tf_status tf_mingru_create(const tf_mingru_config *cfg, const float *
         const int din = l == 0 ? d : 2 * H;
         const MGeom g = stage_bytes_of(op, din);
         const float *W = lw, *b = lw + (size_t)4 * H * din;
+        if (!half) h->wide = h->wide || any_beyond(W, (size_t)4 * H * din, kWideWeight);
         // layered: for each 32-channel chunk and direction the gate block starts a
         // stage; the candidate block follows it in the same stage (merged) or starts
         // the next one.  Fused: layer 0 merged (candidate first), layer 1 one block per
@@ -1242,27 +1275,27 @@ tf_status mingru_states(const float *hits, int64_t n_hits, const int32_t *offset
         switch (h->op) {
             case OP_BF16:
                 if (H == 192)
-                    e = din == 128 ? launch_last<OP_BF16, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                   : launch_last<OP_BF16, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 128 ? launch_last<OP_BF16, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream)
+                                   : launch_last<OP_BF16, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream);
                 else
-                    e = din == 32 ? launch_last<OP_BF16, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                  : launch_last<OP_BF16, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 32 ? launch_last<OP_BF16, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream)
+                                  : launch_last<OP_BF16, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream);
                 break;
             case OP_F16:
                 if (H == 192)
-                    e = din == 128 ? launch_last<OP_F16, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                   : launch_last<OP_F16, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 128 ? launch_last<OP_F16, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream)
+                                   : launch_last<OP_F16, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream);
                 else
-                    e = din == 32 ? launch_last<OP_F16, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                  : launch_last<OP_F16, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 32 ? launch_last<OP_F16, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream)
+                                  : launch_last<OP_F16, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream);
                 break;
             default:
                 if (H == 192)
-                    e = din == 128 ? launch_last<OP_F32, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                   : launch_last<OP_F32, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 128 ? launch_last<OP_F32, 128, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream)
+                                   : launch_last<OP_F32, 384, 192>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream);
                 else
-                    e = din == 32 ? launch_last<OP_F32, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream)
-                                  : launch_last<OP_F32, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->err, h->cu_count, stream);
+                    e = din == 32 ? launch_last<OP_F32, 32, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream)
+                                  : launch_last<OP_F32, 128, 64>(last, xin, rows, n_hits, offsets, n_tracks, sg, yout, states, h->wide, h->err, h->cu_count, stream);
                 break;
         }
         if (e != hipSuccess) return TF_EHIP;

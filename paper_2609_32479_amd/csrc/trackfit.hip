@@ -62,7 +62,7 @@ namespace {
 // ---------------------------------------------------------------------------
 template <int D, int OP, int HT_, bool PAIR_ = false>
 struct KCfg {
-    static constexpr bool HALF = OP != OP_F32;
+    static constexpr bool HALF = is_half(OP);
     static constexpr int HT = HT_;               // 32-hit tiles per wave tile
     static constexpr int CAP = 32 * HT;          // hit slots per wave tile
     static constexpr int SP = 16 * HT;           // positions per stream (2 streams)
@@ -1477,6 +1477,14 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                                 float v[8];
 #pragma unroll
                                 for (int u = 0; u < KL; ++u) v[u] = pblk[prow * C::STS + kb * K + hh * KL + u];
+                                if constexpr (OP == OP_F32) {
+                                    if (const unsigned wm = wide_mask(max_abs(0.f, v))) {
+                                        const FT b = take_wide(v, (wm >> cc) & 1u);
+#pragma unroll
+                                        for (int mu = 0; mu < MT; ++mu)
+                                            hid[mu] = Frag<OP_F32W>::mma(w1[((bl * KPB + kb) * MT + mu) * 64 + lane], b, hid[mu]);
+                                    }
+                                }
                                 FT b_hi, b_lo;
                                 split_operand<F>(v, b_hi, b_lo);
 #pragma unroll
@@ -1570,9 +1578,13 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                     float v[8];
 #pragma unroll
                     for (int u = 0; u < KL; ++u) v[u] = hid[ks / RPK][(ks % RPK) * KL + u];
+                    const FT a = w2[ks * 64 + lane];
+                    if constexpr (OP == OP_F32) {
+                        if (const unsigned wm = wide_mask(max_abs(0.f, v)))
+                            o = Frag<OP_F32W>::mma(a, take_wide(v, (wm >> cc) & 1u), o);
+                    }
                     FT b_hi, b_lo;
                     split_operand<F>(v, b_hi, b_lo);
-                    const FT a = w2[ks * 64 + lane];
                     F::mma(a, b_hi, o, osm);
                     if constexpr (C::HALF) o = F::mma(a, b_lo, o);
                 }
@@ -1692,6 +1704,7 @@ Geom geom_d(int D, int ht) {
 
 struct tf_weights {
     int n_layers = 0, d = 0, dtype = 0, max_hits = 0, device = 0, cu_count = 0, n_feat = 0;
+    bool wide = false;  // fp32 weights beyond the limits of the part products (Frag<OP_F32W>)
     void *dmem = nullptr;
     int *err = nullptr;
     DevParams params{};
@@ -1948,6 +1961,19 @@ extern "C" tf_status tf_weights_create(const tf_config *cfg, const float *blob, 
         return TF_EHIP;
     }
     char *b = static_cast<char *>(wt->dmem);
+    if (!half) {
+        bool wide = any_beyond(fW, NFEAT ? dd * KF32 : 0, kWideWeight) || any_beyond(W1, dd * dd, kWideWeight) ||
+                    any_beyond(W2, 5 * dd, kWideWeight);
+        for (int l = 0; l < L; ++l) {
+            const float *Wi = inW_of(l), *g = g_of(l);
+            wide = wide || any_beyond(inb_of(l), 2 * dd, kWideBias) || any_beyond(outW_of(l), 2 * dd * dd, kWideWeight);
+            for (size_t i = 0; i < 2 * dd * dd && !wide; ++i) {
+                const float v = (float)((double)Wi[i] * g[i % dd]);
+                wide = any_beyond(&v, 1, kWideWeight);
+            }
+        }
+        wt->wide = wide;
+    }
     wt->n_layers = L;
     wt->d = D;
     wt->dtype = cfg->dtype;
@@ -1990,7 +2016,7 @@ hipError_t launch_ht(const float *hits, int64_t n_hits, const int32_t *offsets, 
                      const tf_weights *w, float *out, long long out_rows, hipStream_t stream) {
     if constexpr (D <= 128) {
         if (w->max_hits == 64) {
-            if constexpr (OP != OP_F32 && OUTM == OUT_HEAD)
+            if constexpr (is_half(OP) && OUTM == OUT_HEAD)
                 return launch<D, OP, 1, OUTM, FOURIER, true>(hits, n_hits, offsets, n_tracks, w, out, out_rows, stream);
             return launch<D, OP, 2, OUTM, FOURIER>(hits, n_hits, offsets, n_tracks, w, out, out_rows, stream);
         }
@@ -2007,9 +2033,13 @@ hipError_t launch_d(const float *hits, int64_t n_hits, const int32_t *offsets, i
         case TF_BF16_F16ACT:
             return launch_ht<D, OP_F16, OUTM, FOURIER>(hits, n_hits, offsets, n_tracks, w, out, out_rows, stream);
         default:
-            if constexpr (D <= 128)
+            if constexpr (D <= 128) {
+                if (w->wide)
+                    return launch_ht<D, OP_F32W, OUTM, FOURIER>(hits, n_hits, offsets, n_tracks, w, out, out_rows,
+                                                                stream);
                 return launch_ht<D, OP_F32, OUTM, FOURIER>(hits, n_hits, offsets, n_tracks, w, out, out_rows,
                                                            stream);
+            }
             return hipErrorNotSupported;
     }
 }
