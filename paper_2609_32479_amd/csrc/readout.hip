@@ -235,14 +235,19 @@ inline bool head16_in_lds(int d, int hidden) {
 // lie on different compute units.
 // 262 144 tracks of the paper's head: 168 -> 114 us (2.7 -> 4.1 TB/s; a large
 // copy reaches 4.7).
-// LDSW: the weights in LDS; otherwise they are read from memory by each wave.
+// LDSW: the weights in LDS; otherwise each wave reads them for its one tile and is a
+// workgroup of its own, so that few tiles lie on different compute units (eight waves
+// that read up to 390 KB of weights through one unit's cache are slower than eight units)
+// and a launch's last tiles do not wait for room for eight waves.  Workgroups of eight,
+// one: hidden = 256 on d = 256, 500 tracks 43.5, 23.4 us, 20 011 51.2, 36.0, 66 001 100,
+// 79; hidden = 192 on d = 192 32.2, 16.8, 35.9, 23.1, 69.9, 54.4 (of two: in between).
 template <int MT, bool LDSW>
-__global__ __launch_bounds__(64 * kWaves16) void tf_readout16_kernel(const float *__restrict__ states, int n, int D,
+__global__ __launch_bounds__(LDSW ? 64 * kWaves16 : 64, 2) void tf_readout16_kernel(const float *__restrict__ states, int n, int D,
                                                                      const double *__restrict__ seeds,
                                                                      const char *__restrict__ weights,
                                                                      float *__restrict__ quant,
                                                                      double *__restrict__ out) {
-    __shared__ __attribute__((aligned(16))) char smem[LDSW ? kLdsBytesMax : kWaves16 * kQBytes];
+    __shared__ __attribute__((aligned(16))) char smem[LDSW ? kLdsBytesMax : kQBytes];
     const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6);
     const int s = lane >> 5, c = lane & 31;
     const Head16 L = head16(D, 32 * MT);
@@ -261,7 +266,7 @@ __global__ __launch_bounds__(64 * kWaves16) void tf_readout16_kernel(const float
 
     // (!LDSW: one tile per wave, since nothing would be kept for the next)
     const int tiles = (n + 31) / 32, step = (int)gridDim.x * kWaves16;
-    int tile = LDSW ? wv * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kWaves16 + wv;
+    int tile = LDSW ? wv * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x;
     // this lane's row of a tile, from its half of the first k-step on (columns past the
     // batch repeat the tile's first track, in bounds; their results are dropped)
     auto row = [&](int tl) {
@@ -376,13 +381,12 @@ void launch_mt(const tf_readout *h, hipStream_t stream, const float *states, int
                double *out) {
     if (h->half) {
         const int tiles = (n + 31) / 32;
-        const dim3 block(64 * kWaves16);
         if (head16_in_lds(h->d, h->hidden))  // one workgroup per compute unit, no more than tiles
-            hipLaunchKernelGGL((tf_readout16_kernel<MT, true>), dim3((unsigned)std::min(tiles, h->cu_count)), block, 0,
-                               stream, states, n, h->d, seeds, h->dmem, quant, out);
+            hipLaunchKernelGGL((tf_readout16_kernel<MT, true>), dim3((unsigned)std::min(tiles, h->cu_count)),
+                               dim3(64 * kWaves16), 0, stream, states, n, h->d, seeds, h->dmem, quant, out);
         else
-            hipLaunchKernelGGL((tf_readout16_kernel<MT, false>), dim3((unsigned)((tiles + kWaves16 - 1) / kWaves16)),
-                               block, 0, stream, states, n, h->d, seeds, h->dmem, quant, out);
+            hipLaunchKernelGGL((tf_readout16_kernel<MT, false>), dim3((unsigned)tiles), dim3(64), 0, stream, states, n,
+                               h->d, seeds, h->dmem, quant, out);
     } else {
         const int per_block = 32 * kWaves;
         const dim3 grid((unsigned)((n + per_block - 1) / per_block)), block(64 * kWaves);
