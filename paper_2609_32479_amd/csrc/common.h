@@ -202,9 +202,9 @@ __device__ __forceinline__ bf16x8x3 take_wide(float *v, bool wide) {
 }
 // On the host: whether any of n weights (or biases) is beyond the limit.
 inline bool any_beyond(const float *w, size_t n, float limit) {
-    for (size_t i = 0; i < n; ++i)
-        if (!(__builtin_fabsf(w[i]) < limit)) return true;
-    return false;
+    bool any = false;
+    for (size_t i = 0; i < n; ++i) any |= !(__builtin_fabsf(w[i]) < limit);  // (no early exit: vectorised)
+    return any;
 }
 // The split of OP_F32 on the host (the weights): the parts' bf16 bits.  From 2^127 on h is
 // cut off (rounded it might be infinite); infinity and NaN have no further parts.
@@ -224,9 +224,12 @@ inline Bf16Parts bf16_parts(float v) {
     };
     // to the nearest bf16, ties to even
     auto near = [](uint32_t u) { return (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u; };
-    if (v != v) return {{0x7fc0, 0, 0}};
-    if (__builtin_isinf(v)) return {{uint16_t(bits(v) >> 16), 0, 0}};
-    const uint32_t h = __builtin_fabsf(v) < 0x1p127f ? near(bits(v)) : bits(v) & 0xffff0000u;
+    uint32_t h = near(bits(v));
+    if (!(__builtin_fabsf(v) < 0x1p127f)) {
+        if (v != v) return {{0x7fc0, 0, 0}};
+        h = bits(v) & 0xffff0000u;
+        if (__builtin_isinf(v)) return {{uint16_t(h >> 16), 0, 0}};
+    }
     const float r = v - value(h);
     const uint32_t m = near(bits(r));
     return {{uint16_t(h >> 16), uint16_t(m >> 16), uint16_t(bits(r - value(m)) >> 16)}};

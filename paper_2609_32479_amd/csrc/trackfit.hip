@@ -1967,10 +1967,9 @@ extern "C" tf_status tf_weights_create(const tf_config *cfg, const float *blob, 
         for (int l = 0; l < L; ++l) {
             const float *Wi = inW_of(l), *g = g_of(l);
             wide = wide || any_beyond(inb_of(l), 2 * dd, kWideBias) || any_beyond(outW_of(l), 2 * dd * dd, kWideWeight);
-            for (size_t i = 0; i < 2 * dd * dd && !wide; ++i) {
-                const float v = (float)((double)Wi[i] * g[i % dd]);
-                wide = any_beyond(&v, 1, kWideWeight);
-            }
+            for (size_t row = 0; row < 2 * dd; ++row)  // (the gain is folded in)
+                for (size_t c = 0; c < dd; ++c)
+                    wide |= !(std::fabs((float)((double)Wi[row * dd + c] * g[c])) < kWideWeight);
         }
         wt->wide = wide;
     }
