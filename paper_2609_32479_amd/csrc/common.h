@@ -88,7 +88,7 @@ template <> struct Frag<OP_F16> {
 // against 64 bits: 65 536 tracks, four layers of 128: 1.9e-7 (one sum 2.9e-7); the
 // minGRU of 40 000: 1.5e-7 (3.2e-7).
 // Cycles of 16 terms: 192 against 512 of the fp32 instruction.  65 536 tracks through
-// the d = 128 encoder take 2.80 ms, 40 000 through the minGRU 3.06 (one sum 2.72 and 2.96,
+// the d = 128 encoder take 2.87 ms, 40 000 through the minGRU 3.06 (one sum 2.71 and 2.96,
 // the fp32 instruction 5.49 and 6.77).  All eight products above 2^-30, with parts cut
 // off: 0.424 units for one term, but 3.60 and 3.81 ms.
 struct bf16x8x3 {
@@ -140,7 +140,7 @@ template <> struct Frag<OP_F32> {
 // fp32 operands that may be infinite, or so large that part products overflow: h m and
 // h l of an infinite h are infinite or NaN where the product is neither, and parts of
 // different signs overflow to different infinities.  They are put together again and
-// multiplied by the fp32 instruction (8 of 64 cycles for 16 terms).
+// multiplied by the fp32 instruction (eight of depth 2, 512 cycles for 16 terms).
 // It runs where weights or operands are beyond the limits here, below which no sum of
 // up to 384 products can overflow: a handle with such weights takes it throughout, and
 // the places that see operands without a bound (the minGRU's input rows, the head's
@@ -560,7 +560,10 @@ __device__ __forceinline__ int group_begin(const int *__restrict__ offsets, int 
 // several in a row on a few.  A tile's walk through the layers is what a small
 // call costs: with at least 8 tracks per wave (6 workgroups for 500 tracks) the
 // four-layer d = 128 encoder took 243 us for 500 tracks, spread over the chip
-// 39 us; from about 20 000 tracks on both rules fill the chip.
+// 39 us; from about 20 000 tracks on both rules fill the chip.  Calls on several streams
+// then take turns instead of sharing the chip, which costs less than it gains: 3 072
+// tracks 290 -> 58 us a call on one stream, on four streams 145 -> 55 us a call (500
+// tracks 123 -> 36, 14 000 207 -> 168; the backbone and the fp32 and 64-hit encoders alike).
 inline unsigned workgroups(int n_tracks, int cu_count) {
     return (unsigned)(n_tracks < cu_count ? (n_tracks < 1 ? 1 : n_tracks) : cu_count);
 }

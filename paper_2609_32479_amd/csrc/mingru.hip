@@ -309,7 +309,7 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
         unsigned sb0 = 0, sb1 = 0, eb0 = 0, eb1 = 0, st0 = 0, st1 = 0;
         FT xa[KIN];
         // fp32: operand rows that the fp32 instruction multiplies (see Frag<OP_F32W>); their
-        // operands here are 0
+        // part operands are 0
         unsigned wide = wide_weights ? ~0u : 0u;
         if (work) {
             mg_tile_meta(smask, n, row0, lane, t_start, t_off, rowmap, sb0, sb1, eb0, eb1, st0, st1);
@@ -460,7 +460,7 @@ void tf_mingru_kernel(const typename Frag<OP>::E *__restrict__ X, long long x_ro
                 // need the gate block alone: the update adds a x and keeps 1 - a of the state.
                 // (With the gates after both blocks the fp32 layer of input 384, one wave per
                 // SIMD, kept the matrix cores busy 39 % of the time; 40 000 tracks through the
-                // fp32 model 3.35 -> 3.00 ms.)
+                // fp32 model 3.35 -> 3.00 ms, both with the products in one sum.)
                 constexpr int XOFF = C::MERGE ? C::BLOCK : 0;
                 float CF[SP];
                 if constexpr (!C::HALF) {

@@ -233,7 +233,7 @@ inline bool head16_in_lds(int d, int hidden) {
 // waves per SIMD.
 // Tile t is wave t / grid of workgroup t % grid in the first turn, so that few tiles
 // lie on different compute units.
-// 262 144 tracks of the paper's head: 168 -> 114 us (2.7 -> 4.1 TB/s; a large
+// 262 144 tracks of the paper's head: 168 -> 112 us (2.7 -> 4.1 TB/s; a large
 // copy reaches 4.7).
 // LDSW: the weights in LDS; otherwise each wave reads them for its one tile and is a
 // workgroup of its own, so that few tiles lie on different compute units (eight waves

@@ -18,12 +18,15 @@
 // What bounds it: vector instructions, then memory.  With the library's atan2,
 // sqrt and asinhf a row took about 440 vector instructions (340 of them the two
 // asinhf) and the seed of 32 tracks 800 on half the lanes; 1 048 576 tracks (14.7 M
-// hits, 0.40 GB in and out) took 225 us, 1.8 TB/s.  Here a row takes about 160
+// hits, 0.40 GB in and out) took 226 us, 1.8 TB/s.  Now a row takes about 160
 // (arc_length and asinh32 below) and lanes i and i + 32 of a wave share track i's
-// seed: each takes the arc of one hit and one of the two angles: 144 us, 2.8 TB/s,
+// seed: each takes the arc of one hit and one of the two angles: 150 us, 2.7 TB/s,
 // still bound by the vector unit (one or two waves a workgroup, or five per SIMD
-// instead of four, change nothing); the quarter-rate instructions (fp64
-// reciprocals, roots, conversions, scalings) are about a third of a row.
+// instead of four, change nothing).  Of the 1 960 vector instructions of a wave (a
+// counter's figure, 14 hits a track) the 7 to 7.5 chunks of 64 rows take 1 120 to 1 200,
+// a third of these at quarter rate (fp64 reciprocals, roots, conversions, scalings);
+// the other 40 % are the seed itself (the library's atan2, three of its square roots,
+// six fp64 divisions) and the rows' way to their tracks.
 //
 // Reads: a wave's rows are one contiguous range.  When it spans at most
 // kSeedRows rows (and the wave's offsets are in order), the wave reads it once,
@@ -78,7 +81,7 @@ __device__ __forceinline__ double div64(double a, double b) {
 // library's asinhf on the rounded argument; this one stays at 0.29, the rounding
 // of the result).
 __device__ __forceinline__ float asinh32(double x) {
-    const bool over = fabs(x) > 3.4028234663852886e38;  // not an fp32 value: infinite
+    const bool over = fabs(x) >= 3.4028235677973366e38;  // rounds to no fp32 value: infinite
     const double t = over ? 1.0 : fabs(x), z = t * t;
     double p = 0.00993445135043325;
     p = fma(p, z, -0.02052563251636141);

@@ -350,7 +350,8 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
     constexpr int MAXTR = C::MAXTR, TMAXTR = C::TMAXTR;
     constexpr int OUTW = STATES ? 2 * D : 5;  // floats per output row (head, states)
     // weight fragments on their way (ring_products), as many as the registers allow
-    // without scratch (fp32: 65 536 tracks 2.77 ms without, 2.88 ms with two)
+    // without scratch (fp32, products in one sum: 65 536 tracks 2.77 ms without, 2.88 ms
+    // with two; in two sums there are fewer registers left)
     constexpr int kRing = !C::HALF ? 0 : D <= 128 ? 4 : OUTM == OUT_HEAD ? 3 : 0;
 
     __shared__ __attribute__((aligned(16))) char smem[C::LDS_BYTES];
@@ -793,8 +794,8 @@ void tf_encoder_kernel(const float *__restrict__ hits, long long n_hits_total, c
                             gx[i / 16][i % 16] = exp_clamped(-__builtin_amdgcn_fmed3f(g + bgv, -80.0f, 80.0f));
                     };
                     // (One tile of 32 rows and the pooled head: the others have no registers left
-                    // for it; fp32, two waves per SIMD: 65 536 tracks 2.77 ms without, 2.83 ms
-                    // with it.)
+                    // for it; fp32, two waves per SIMD, products in one sum: 65 536 tracks 2.77 ms
+                    // without, 2.83 ms with it.)
                     constexpr bool BESIDE = C::HALF && HT == 1 && OUTM == OUT_HEAD;
                     constexpr int NE = HT * 16;
                     f32x16 small[HT];
