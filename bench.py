@@ -50,42 +50,42 @@ COPY_MIB = 256  # plain copy kernel used to calibrate the HBM byte counters
 # only while the SHA-256 of the listed kernel sources, concatenated, is the one
 # recorded and the launch shape is the recorded one; otherwise traffic is null.
 ENCODER_SRCS = ("trackfit.hip", "common.h")
-_ENC_SHA = "03e1d19e9cfae1e6cc4e58be2f7d10039fa15c30ceb82f4b6f7b52c4b856a3d3"
+_ENC_SHA = "21be6f5d1583b2337c85b9d634d8b2b93edf6265fd250421ef3874652d9ed05a"
 TRAFFIC = {
     # "profile": the summary in profiles/ that these figures come from (its
     # trace, counter runs and bench line were taken on one box in one session)
     ("encoder", "deploy_d128x4_bf16_8m"): {
         "srcs": ENCODER_SRCS, "batch": 262144, "calls_per_step": 32, "sha256": _ENC_SHA,
-        "fetch_bytes": 53177331, "write_bytes": 5578880,
+        "fetch_bytes": 53122677, "write_bytes": 5523648,
         # rocprofv3's derived MfmaUtil (matrix-unit busy cycles over SIMD cycles) and
         # VALUBusy (cycles issuing vector instructions), medians over launches
-        "mfma_util": 0.367, "valu_busy": 0.582,
+        "mfma_util": 0.370, "valu_busy": 0.592,
         "profile": "profiles/tf_encoder_kernel_deploy_d128x4_bf16_8m.md"},
     ("encoder", "fourier15_deploy_d128x4_bf16_8m"): {
         "srcs": ENCODER_SRCS, "batch": 262144, "calls_per_step": 32, "sha256": _ENC_SHA,
-        "fetch_bytes": 233133847, "write_bytes": 9522144, "mfma_util": 0.383, "valu_busy": 0.559,
+        "fetch_bytes": 235445284, "write_bytes": 8892752, "mfma_util": 0.383, "valu_busy": 0.565,
         "profile": "profiles/tf_encoder_kernel_fourier15_deploy_d128x4_bf16_8m.md"},
     ("encoder", "d128x4_fp32_65k"): {
         "srcs": ENCODER_SRCS, "batch": 65536, "calls_per_step": 1, "sha256": _ENC_SHA,
-        "fetch_bytes": 22474213, "write_bytes": 1520192, "mfma_util": 0.656, "valu_busy": 0.175,
+        "fetch_bytes": 27466413, "write_bytes": 1875808, "mfma_util": 0.471, "valu_busy": 0.379,
         "profile": "profiles/tf_encoder_kernel_d128x4_fp32_65k.md"},
     ("encoder", "d256x6_bf16_1m"): {
         "srcs": ENCODER_SRCS, "batch": 1048576, "calls_per_step": 1, "sha256": _ENC_SHA,
-        "fetch_bytes": 478426450, "write_bytes": 88989104, "mfma_util": 0.434, "valu_busy": 0.351,
+        "fetch_bytes": 305690504, "write_bytes": 47877088, "mfma_util": 0.469, "valu_busy": 0.375,
         "profile": "profiles/tf_encoder_kernel_d256x6_bf16_1m.md"},
     ("encoder", "long64_d128x4_bf16_200k"): {
         "srcs": ENCODER_SRCS, "batch": 200000, "calls_per_step": 1, "sha256": _ENC_SHA,
-        "fetch_bytes": 162485638, "write_bytes": 4057664, "mfma_util": 0.295, "valu_busy": 0.545,
+        "fetch_bytes": 162434056, "write_bytes": 4025856, "mfma_util": 0.332, "valu_busy": 0.540,
         "profile": "profiles/tf_encoder_kernel_long64_d128x4_bf16_200k.md"},
     ("readout", "deploy_d128x4_bf16_8m"): {
         "srcs": ENCODER_SRCS, "batch": 262144, "calls_per_step": 32, "sha256": _ENC_SHA,
-        "fetch_bytes": 59044752, "write_bytes": 270794752, "mfma_util": 0.326, "valu_busy": 0.602,
+        "fetch_bytes": 61656334, "write_bytes": 270008320, "mfma_util": 0.334, "valu_busy": 0.640,
         "profile": "profiles/readout_path_deploy_d128x4_bf16_8m.md"},
     ("paper", "mingru2_h192_fourier15_deploy_bf16_8m"): {
         # the backbone call: one tf_backbone_kernel launch (front end and both layers)
         "srcs": ENCODER_SRCS + ("mingru.hip",), "batch": 262144, "calls_per_step": 32,
-        "sha256": "e4a021b3ba6e36bab6b1991c81e2f8484491bd1bef565a312373c60ec51d6e10",
-        "fetch_bytes": 255927980, "write_bytes": 402653184, "mfma_util": 0.332, "valu_busy": 0.360,
+        "sha256": "e261895ab761223044547f503ef27596cdae8b180a511c3eac0e9b3340157e2b",
+        "fetch_bytes": 246204174, "write_bytes": 402653184, "mfma_util": 0.408, "valu_busy": 0.427,
         "profile": "profiles/paper_model_mingru2_h192_fourier15_deploy_bf16_8m.md"},
 }
 
@@ -241,8 +241,8 @@ SEED_SRC = os.path.join(ROOT, "paper_2609_32479_amd", "csrc", "seed.hip")
 # FETCH_SIZE / WRITE_SIZE runs of this script's seed path with --copy-calibration
 # (scaled as for the encoder); valid only for the recorded source.
 SEED_TRAFFIC = {"workload": "deploy_d128x4_bf16_8m", "n_tracks": 8388608,
-                "kernel_sha256": "e1a3819882b73f490ea59aa680513cee1e3ad35b038193b373f2bfb5c83660a4",
-                "fetch_bytes": 1460226274, "write_bytes": 1756872480}
+                "kernel_sha256": "c70bef309a751a3a88cdef9b3ed72ae8f6ae7c319bca569de9350d518b37ab91",
+                "fetch_bytes": 1460012716, "write_bytes": 1757969936}
 
 
 def seed_algorithmic_bytes(n_hits, n_tracks):
